@@ -226,6 +226,34 @@ constexpr int PF_ER = 4;  // ring of list entries: tile kt+2 is fetched while kt
 
 typedef __attribute__((address_space(3))) void* lds_ptr_t;
 
+// Work order.  Workgroup x is dispatched to XCD x mod 8.  Each XCD takes
+// nbh / 8 of the (sequence, head) slices whole, in groups of PF_GROUP that
+// share its L2.  Inside a group the blocks go heaviest first: every slice's
+// last query block (the most visible keys), then every slice's block before
+// it, and so on, so that the light blocks fill the end of the launch instead
+// of one slice's heavy block running alone there.  The nbh mod 8 slices left
+// over come first, their blocks dealt over all XCDs, heaviest first.  (One
+// contiguous range of blocks per XCD, in groups of 8 slices whatever their
+// number, gave half the XCDs the heavy half of each group below 64 slices:
+// 32 slices of 16384 tokens at d = 64 took 822 us, and 665 us in this order;
+// 256 and 512 slices, whose groups fell whole to one XCD, take the same.)
+__device__ __forceinline__ void work_item(int x, int nbh, int n_qt, int* bh, int* qt) {
+  const int per = nbh >> 3, rem = nbh & 7;
+  const int first = rem * n_qt;
+  if (x < first) {
+    *bh = 8 * per + x % rem;
+    *qt = n_qt - 1 - x / rem;
+    return;
+  }
+  const int y = x - first;
+  const int xcd = y & 7, idx = y >> 3;
+  const int grp = idx / (PF_GROUP * n_qt);
+  const int gsz = min(PF_GROUP, per - grp * PF_GROUP);
+  const int in_grp = idx - grp * PF_GROUP * n_qt;
+  *bh = xcd * per + grp * PF_GROUP + in_grp % gsz;
+  *qt = n_qt - 1 - in_grp / gsz;
+}
+
 // ---------------------------------------------------------------------------
 // main kernel
 // ---------------------------------------------------------------------------
@@ -251,23 +279,8 @@ __device__ __forceinline__ void prefill_attn_body(
   __shared__ int32_t row_ring[PF_ER][PF_BK];  // bare row index per entry
   __shared__ TileInfo info_ring[PF_ER];
 
-  // Work order.  Workgroup x is dispatched to XCD x mod 8, and each XCD takes
-  // a contiguous range of work items in dispatch order, so the items of a
-  // group of PF_GROUP consecutive (sequence, head) slices share that XCD's
-  // L2.  Inside a group the items go heaviest first: every head's last
-  // query block (the most visible keys), then every head's block before it,
-  // and so on, so that the light blocks fill the end of the launch instead
-  // of one slice's heavy block running alone there.
-  const int x = blockIdx.x;
-  const int xcd = x & 7, idx = x >> 3;
-  const int qn = n_work >> 3, rem = n_work & 7;
-  const int work = xcd * qn + min(xcd, rem) + idx;
-  const int nbh = n_work / n_qt;
-  const int grp = work / (PF_GROUP * n_qt);
-  const int gsz = min(PF_GROUP, nbh - grp * PF_GROUP);
-  const int in_grp = work - grp * PF_GROUP * n_qt;
-  const int bh = grp * PF_GROUP + in_grp % gsz;
-  const int qt = n_qt - 1 - in_grp / gsz;
+  int bh, qt;
+  work_item(blockIdx.x, n_work / n_qt, n_qt, &bh, &qt);
   const int s = bh / H;
   // query rows are local (0 .. L-1); their tokens start at tok0 (cached) or 0
   const int tok0 = CACHED ? cc.tok0 : 0;
