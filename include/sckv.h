@@ -304,13 +304,17 @@ int kv_compact(void* kv, void* kv_out, int32_t M, int32_t b, int32_t H, int32_t 
  * kv_len, cur_tok    : [b].   vu, pos: [b][L_meta].
  * ws     : device workspace >= sckv_decode_workspace_bytes(b, H, L_cap, d_head)
  *          holding the split-K partials (overwritten; calls that share a
- *          workspace must be ordered, e.g. enqueued on one stream).
+ *          workspace must be ordered, e.g. enqueued on one stream).  A larger
+ *          one lets launches of few slices be split finer; room for 512
+ *          partials of d_head + 2 floats is as much as is used beyond the
+ *          required size.
  * status : nullable int32, status bits OR-ed in.
- * Launch shape: with b*H >= 512 one workgroup per (sequence, head) covers
- * all its rows and writes o (the workspace is not touched); with fewer, the
- * rows are cut into balanced chunks of at most about 1024 rows, one
- * workgroup each, and a second kernel merges the chunk partials
- * (log-sum-exp) into o.  bf16 scores are computed on the matrix cores with
+ * Launch shape: bf16 with b*H >= 256 slices, or with fewer over caches of
+ * at most 512 + 8 * b*H rows, and fp32 with b*H >= 512: one workgroup per
+ * (sequence, head) covers all its rows and writes o (the workspace is not
+ * touched).  Otherwise the rows are cut into balanced chunks of at most about
+ * 1024 rows, one workgroup each, and a second kernel merges the chunk
+ * partials (log-sum-exp) into o.  bf16 scores are computed on the matrix cores with
  * q carried as two bf16 terms (about fp32 accuracy).
  * ------------------------------------------------------------------------- */
 size_t sckv_decode_workspace_bytes(int32_t b, int32_t H, int32_t L_cap, int32_t d_head);

@@ -18,6 +18,7 @@
 //   device-wide cache flush inside the chunk kernel.
 #include <math.h>
 
+#include <algorithm>
 #include <cmath>
 #include <mutex>
 #include <string>
@@ -26,23 +27,40 @@
 
 namespace sckv {
 
-// Launch shapes, measured on MI355X over three decode shapes: 2048 slices of
-// about 560 rows (d=64), 512 slices of about 2100 rows (d=80, rotary) and
-// 8192 slices of about 1200 rows (d=80, rotary).  A slice is one (sequence,
-// head) pair.
-//  * Fewer than DEC_SINGLE_MIN slices: each slice is cut into chunks of
-//    about DEC_CH rows, one 4-wave workgroup each, and a second kernel merges
-//    the chunk partials.
+// Launch shapes, measured on MI355X.  A slice is one (sequence, head) pair.
+//  * bf16, few slices (below DEC_ONE_MIN) of a long cache: each slice is cut
+//    into chunks, one 4-wave workgroup each, and a second kernel merges the
+//    chunk partials.  A chunk has about DEC_CH rows at most; a launch of few
+//    slices is cut finer, to DEC_FILL workgroups or chunks of DEC_CH_MIN rows,
+//    as far as the workspace holds the partials (32 slices of 1000 rows,
+//    d = 80: 18.2 us in chunks of DEC_CH, 9.6 us in chunks of 128; a target of
+//    1024 workgroups was up to 27% slower, one of 256 within 3%).
 //  * Otherwise one workgroup per slice writes the output itself (no second
-//    launch).  fp32: 512 threads below DEC_NARROW_MIN slices, 256 from there
-//    on.  bf16: the most waves per slice (4, 2 or 1; 1 only where d <= 64)
-//    with which every wave of the launch is resident at once (the kernel
-//    holds two waves per SIMD), so the launch runs in one round; where even
-//    one wave per slice exceeds that, 4 waves, whose shorter workgroups
-//    balance the rounds best.  Measured: 512 slices (d=80) 4 waves; 2048
-//    slices (d=64) 1 wave 2% faster than 2 and 4% faster than 4; 8192
-//    slices (d=80) 4 waves 2.5% faster than 2.
+//    launch).  256 slices of 1000 / 3000 rows (d = 64) took 18.2 / 42.8 us
+//    split and 13.7 / 37.8 us so, 480 slices of 300 (d = 64) / 3000 rows
+//    (d = 80) 15.4 / 92.1 and 10.9 / 86.2 us.  Below 256 slices it depends on
+//    the rows (128 slices, d = 80: 1000 rows 16.5 split, 14.7 so; 2000 rows
+//    23.0 and 24.7; 32 slices: 300 rows 8.5 and 6.6, 1000 rows 9.6 and 11.3),
+//    of which the host knows the cache's capacity: at most
+//    DEC_ONE_ROWS + DEC_ONE_ROWS_PER_SLICE * slices rows.
+//    Waves per slice: the most (8, 4, 2 or 1; 8 only for caches of more than
+//    DEC_EIGHT_ROWS rows, 1 only where d <= 64) with which every wave of the
+//    launch is resident at once (the kernel holds two waves per SIMD), so the
+//    launch runs in one round; where even one wave per slice exceeds that, 4
+//    waves, whose shorter workgroups balance the rounds best.  Measured: 256
+//    slices of 1000 rows (d = 64) 14.3 us with 4 waves, 13.7 with 8, of 500
+//    rows (d = 80) 11.4 and 12.0; 512 slices (d = 80) 4 waves; 2048 slices
+//    (d = 64) 1 wave 2% faster than 2 and 4% faster than 4; 8192 slices
+//    (d = 80) 4 waves 2.5% faster than 2.
+//  * fp32: split below DEC_SINGLE_MIN slices; from there on one workgroup per
+//    slice of 512 threads, of 256 from DEC_NARROW_MIN slices on.
 constexpr int DEC_CH = 1024;
+constexpr int DEC_CH_MIN = 128;
+constexpr int DEC_FILL = 512;
+constexpr int DEC_ONE_MIN = 256;
+constexpr int DEC_ONE_ROWS = 512;
+constexpr int DEC_ONE_ROWS_PER_SLICE = 8;
+constexpr int DEC_EIGHT_ROWS = 2048;
 constexpr int DEC_SINGLE_MIN = 512;
 constexpr int DEC_NARROW_MIN = 1024;
 constexpr int DEC_WAVES_PER_SIMD = 2;  // decode_mfma_kernel's occupancy (its register count)
@@ -125,8 +143,8 @@ __device__ __forceinline__ int step_kind(const int32_t* cur_tok, const int32_t* 
 // Writes the final output of a slice whose step is not an ordinary append
 // (kind 1: <CL>, the output is v_new; kind 2/3: failure, NaN and a status
 // bit).  `tid` runs over `nthr` threads.
-// A slice's rows split into n chunks of `rows` rows (the last one shorter)
-// of at most about `ch` rows each.  Chunk starts are multiples of 16 rows:
+// A slice's rows split into n chunks of `rows` rows (the last one shorter).
+// Chunk starts are multiples of 16 rows:
 // a wave then reads whole 128-byte lines (a bf16 row of 80 elements is 160
 // bytes, so only every fourth row starts on a line; a chunk that started
 // between would make every load of its wave span one line more).
@@ -134,10 +152,17 @@ struct ChunkPlan {
   int n, rows;
 };
 constexpr int DEC_ALIGN = 16;
-// rows and ch are positive ints, so every sum below fits in 32 unsigned bits
-__device__ __forceinline__ ChunkPlan chunk_plan(int rows, int ch) {
-  const uint32_t r = (uint32_t)rows, c = (uint32_t)ch;
-  const uint32_t n0 = (r + c - 1) / c;
+// How a launch splits its slices: at least one chunk for every DEC_CH rows,
+// and up to `want` chunks of at least DEC_CH_MIN rows; never more than `most`
+// (the partials the workspace holds for a slice).
+struct Split {
+  int32_t want, most;
+};
+// rows is a positive int, so every sum below fits in 32 unsigned bits
+__device__ __forceinline__ ChunkPlan chunk_plan(int rows, Split sp) {
+  const uint32_t r = (uint32_t)rows;
+  const uint32_t fine = min((r + DEC_CH_MIN - 1) / DEC_CH_MIN, (uint32_t)sp.want);
+  const uint32_t n0 = min(max((r + DEC_CH - 1) / DEC_CH, fine), (uint32_t)sp.most);
   const uint32_t per = (r + n0 - 1) / n0;
   const uint32_t cr = (per + DEC_ALIGN - 1) / DEC_ALIGN * DEC_ALIGN;
   ChunkPlan p;
@@ -158,7 +183,7 @@ __device__ __forceinline__ void write_special(int kind, const T* v_new, T* o, in
   }
 }
 
-// FINAL: the workgroup covers the whole slice (one chunk of L_cap rows) and
+// FINAL: the workgroup covers the whole slice (one chunk) and
 // writes the output itself; otherwise it writes a partial for the combine.
 template <typename T, int D, int THREADS, bool FINAL>
 __global__ __launch_bounds__(THREADS) void decode_chunk_kernel(
@@ -167,7 +192,7 @@ __global__ __launch_bounds__(THREADS) void decode_chunk_kernel(
     const int32_t* __restrict__ cur_tok, const int32_t* __restrict__ vu,
     const int32_t* __restrict__ pos, int32_t L_meta, int32_t H, int32_t L_cap, float qscale,
     int rotate, RopeTab tab, float* __restrict__ part, int32_t n_chunk_max, int32_t n_work,
-    int32_t ch, T* __restrict__ o, int32_t* __restrict__ status) {
+    Split sp, T* __restrict__ o, int32_t* __restrict__ status) {
   using C = DecCfg<T, D, THREADS>;
   constexpr int E = C::E, LPR = C::LPR, GRP = C::GRP, RPW = C::RPW, U = C::U, NG = C::NG;
   // chunk-major order: every slice's first chunk is dispatched before any
@@ -184,7 +209,7 @@ __global__ __launch_bounds__(THREADS) void decode_chunk_kernel(
   }
   const int n = kv_len[s];
   const int rows = n + 1;  // cache rows and the new row
-  const ChunkPlan cp = chunk_plan(rows, ch);
+  const ChunkPlan cp = chunk_plan(rows, sp);
   if (chunk >= cp.n) return;
   const int r0 = chunk * cp.rows;
   const int r1 = min(r0 + cp.rows, rows);
@@ -339,31 +364,42 @@ __global__ __launch_bounds__(THREADS) void decode_chunk_kernel(
   }
 }
 
-// One wave per slice: log-sum-exp merge of the slice's chunk partials, 64
-// chunks at a time (lane c holds chunk c's weight; the output elements are
-// spread over the lanes).
+// One workgroup of four waves per slice: log-sum-exp merge of the slice's
+// chunk partials, 64 chunks at a time (lane c holds chunk c's weight; wave w
+// adds chunks w, w + 4, ..., the output elements spread over its lanes; the
+// waves' sums meet in LDS).
+constexpr int COMBINE_WAVES = 4;
 template <typename T, int D>
-__global__ __launch_bounds__(64) void decode_combine_kernel(
+__global__ __launch_bounds__(64 * COMBINE_WAVES) void decode_combine_kernel(
     const T* __restrict__ v_new, const int32_t* __restrict__ kv_len,
     const int32_t* __restrict__ cur_tok, const int32_t* __restrict__ vu, int32_t L_meta,
-    int32_t H, int32_t L_cap, const float* __restrict__ part, int32_t n_chunk_max, int32_t ch,
-    T* __restrict__ o, int32_t* __restrict__ status, int32_t ring) {
+    int32_t H, FastDiv by_H, int32_t L_cap, const float* __restrict__ part, int32_t n_chunk_max,
+    Split sp, T* __restrict__ o, int32_t* __restrict__ status, int32_t ring) {
   const int bh = blockIdx.x;
-  const int s = bh / H;
-  const int lane = threadIdx.x;
-  int kind;
-  if (ring > 0) {  // the ring is always full: only token range and <CL> steps
-    const int t = cur_tok[s];
-    kind = (t < 0 || t >= L_meta) ? 2 : (vu[(int64_t)s * L_meta + t] == t ? 1 : 0);
-  } else {
-    kind = step_kind(cur_tok, vu, kv_len, s, L_meta, L_cap);
+  const int s = fast_div(bh, by_H);
+  const int tid = threadIdx.x;
+  const int lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const float* p = part + (int64_t)bh * n_chunk_max * (D + 2);
+  // the first 64 chunks' maxima and sums are read along with the slice's
+  // length (those past its chunks hold anything and are dropped below)
+  float m0 = -INFINITY, l0 = 0.f;
+  if (lane < n_chunk_max) {
+    m0 = p[lane * (D + 2)];
+    l0 = p[lane * (D + 2) + 1];
   }
+  const int t = cur_tok[s];
+  const int n = ring > 0 ? ring : kv_len[s];  // the ring is always full
+  // the step kind, as step_kind()
+  const int kind = (t < 0 || t >= L_meta)                       ? 2
+                   : vu[(int64_t)s * L_meta + t] == t           ? 1
+                   : (ring == 0 && (n < 0 || n >= L_cap))       ? 3
+                                                                : 0;
   if (kind != 0) {
-    write_special<T, D>(kind, v_new, o, status, bh, H, lane, 64);
+    write_special<T, D>(kind, v_new, o, status, bh, H, tid, 64 * COMBINE_WAVES);
     return;
   }
-  const int nch = chunk_plan((ring > 0 ? ring : kv_len[s]) + 1, ch).n;
-  const float* p = part + (int64_t)bh * n_chunk_max * (D + 2);
+  const int nch = chunk_plan(n + 1, sp).n;
   constexpr int PER = (D + 63) / 64;  // output elements per lane
   float M = -INFINITY, lsum = 0.f, acc[PER];
 #pragma unroll
@@ -372,12 +408,10 @@ __global__ __launch_bounds__(64) void decode_combine_kernel(
     const int c = c0 + lane;
     float mc = -INFINITY, lc = 0.f;
     if (c < nch) {
-      mc = p[c * (D + 2)];
-      lc = p[c * (D + 2) + 1];
+      mc = c0 == 0 ? m0 : p[c * (D + 2)];
+      lc = c0 == 0 ? l0 : p[c * (D + 2) + 1];
     }
-    float mb = mc;
-#pragma unroll
-    for (int off = 32; off > 0; off >>= 1) mb = fmaxf(mb, __shfl_xor(mb, off, 64));
+    const float mb = wave_max(mc);
     const float mn = fmaxf(M, mb);    // finite: every chunk holds a row
     const float sc = exp2f(M - mn);   // 0 on the first block (M = -inf)
     lsum *= sc;
@@ -387,7 +421,7 @@ __global__ __launch_bounds__(64) void decode_combine_kernel(
     lsum = fmaf(lc, w, lsum);
     const int cn = min(64, nch - c0);
 #pragma unroll 4
-    for (int i = 0; i < cn; ++i) {
+    for (int i = wave; i < cn; i += COMBINE_WAVES) {
       const float wi = __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, w), i));
       const float* pc = p + (c0 + i) * (D + 2) + 2;
 #pragma unroll
@@ -396,16 +430,18 @@ __global__ __launch_bounds__(64) void decode_combine_kernel(
     }
     M = mn;
   }
+  lsum = wave_sum(lsum);
+  __shared__ float sums[COMBINE_WAVES][64 * PER];
 #pragma unroll
-  for (int off = 32; off > 0; off >>= 1) lsum += __shfl_xor(lsum, off, 64);
-  const float inv = 1.f / lsum;
+  for (int j = 0; j < PER; ++j) sums[wave][lane + 64 * j] = acc[j];
+  __syncthreads();
+  if (tid < D) {  // every wave holds the whole of lsum
+    float v = 0.f;
 #pragma unroll
-  for (int j = 0; j < PER; ++j) {
-    const int e = lane + 64 * j;
-    if (e < D) {
-      if constexpr (sizeof(T) == 2) o[(int64_t)bh * D + e] = f32_to_bf16(acc[j] * inv);
-      else o[(int64_t)bh * D + e] = acc[j] * inv;
-    }
+    for (int w = 0; w < COMBINE_WAVES; ++w) v += sums[w][tid];
+    v /= lsum;
+    if constexpr (sizeof(T) == 2) o[(int64_t)bh * D + tid] = f32_to_bf16(v);
+    else o[(int64_t)bh * D + tid] = v;
   }
 }
 
@@ -429,7 +465,16 @@ constexpr float DM_RESCALE = 8.f;
 // Sums v[0..NV) over the 32 lanes of each half-wave.  While NV is even a
 // step halves the values a lane keeps (the lane whose MASK bit is set keeps
 // the upper half); odd counts finish with plain butterflies.  On return the
-// lane holds the sums of values [base, base + count).
+// lane holds the sums of values [base, base + count).  Lanes exchange by
+// register moves (row swap, DPP), not through LDS: of the 16-lane rows' moves
+// the half-row mirror stands in for an exchange of lanes 4 apart (its partner
+// differs in the MASK bit, and the two steps after it cover the rest).
+template <int MASK>
+__device__ __forceinline__ float partner(float x) {
+  static_assert(MASK == 8 || MASK == 4 || MASK == 2 || MASK == 1, "within a row of 16 lanes");
+  return dpp_mov<MASK == 8 ? DPP_ROW_ROR8 : MASK == 4 ? DPP_ROW_HALF_MIRROR
+                 : MASK == 2 ? DPP_QUAD_XOR2 : DPP_QUAD_XOR1>(x);
+}
 template <int NV, int MASK>
 __device__ __forceinline__ void half_wave_reduce(float* v, int lane, int& base) {
   if constexpr (MASK > 0) {
@@ -438,15 +483,21 @@ __device__ __forceinline__ void half_wave_reduce(float* v, int lane, int& base) 
       const bool up = (lane & MASK) != 0;
 #pragma unroll
       for (int j = 0; j < HV; ++j) {
-        const float send = up ? v[j] : v[j + HV];
-        const float keep = up ? v[j + HV] : v[j];
-        v[j] = keep + __shfl_xor(send, MASK, 64);
+        if constexpr (MASK == 16) {
+          float a = v[j], b = v[j + HV];
+          swap_rows16(a, b);  // even rows: their and their partner's v[j]; odd rows: v[j + HV]
+          v[j] = a + b;
+        } else {
+          const float send = up ? v[j] : v[j + HV];
+          const float keep = up ? v[j + HV] : v[j];
+          v[j] = keep + partner<MASK>(send);
+        }
       }
       if (up) base += HV;
       half_wave_reduce<HV, MASK / 2>(v, lane, base);
     } else {
 #pragma unroll
-      for (int j = 0; j < NV; ++j) v[j] += __shfl_xor(v[j], MASK, 64);
+      for (int j = 0; j < NV; ++j) v[j] += partner<MASK>(v[j]);
       half_wave_reduce<NV, MASK / 2>(v, lane, base);
     }
   }
@@ -465,8 +516,9 @@ __global__ __launch_bounds__(NW * 64) void decode_mfma_kernel(
     uint16_t* __restrict__ v_cache, const int32_t* __restrict__ kv_len,
     const int32_t* __restrict__ cur_tok, const int32_t* __restrict__ vu,
     const int32_t* __restrict__ pos, int32_t L_meta, int32_t H, int32_t L_cap, float qscale,
-    int rotate, RopeTab tab, float* __restrict__ part, int32_t n_chunk_max, int32_t n_work,
-    int32_t ch, uint16_t* __restrict__ o, int32_t* __restrict__ status, int32_t ring) {
+    int rotate, RopeTab tab, float* __restrict__ part, int32_t n_chunk_max, FastDiv by_H,
+    FastDiv by_slices, int32_t n_bh, Split sp, uint16_t* __restrict__ o,
+    int32_t* __restrict__ status, int32_t ring) {
   constexpr int KS = D / 16;     // k steps of 16 elements
   constexpr int NA = 8 * KS;     // value elements per lane
   constexpr int THREADS = NW * 64;
@@ -476,34 +528,38 @@ __global__ __launch_bounds__(NW * 64) void decode_mfma_kernel(
   static_assert(D >= 64 && D <= 128 && D % 16 == 0 && D <= NW * 64, "head size");
   // chunk-major order (as in decode_chunk_kernel); a one-chunk launch has
   // one workgroup per slice
-  const int n_bh = FINAL ? n_work : n_work / n_chunk_max;
-  const int chunk = FINAL ? 0 : (int)blockIdx.x / n_bh;
-  const int bh = FINAL ? (int)blockIdx.x : (int)blockIdx.x % n_bh;
-  const int s = bh / H;
+  const int chunk = FINAL ? 0 : fast_div(blockIdx.x, by_slices);
+  const int bh = (int)blockIdx.x - chunk * n_bh;
+  const int s = fast_div(bh, by_H);
   const int tid = threadIdx.x;
   const int wave = tid >> 6;
   const int lane = tid & 63;
   const int kr = lane & 31;
   const int h = lane >> 5;
 
-  // Everything the setup reads is wave-uniform and goes through scalar
-  // loads, whose counter is separate from that of the vector loads: the
-  // first two blocks of key/value rows are issued as soon as the slice
-  // length is known and arrive while q is prepared.  The block addresses use
-  // the length clamped into the cache, so they are valid whatever the step
-  // turns out to be.
+  // The slice's length, token and position are wave-uniform and go through
+  // scalar loads, whose counter is separate from that of the vector loads:
+  // the first two blocks of key/value rows are issued as soon as the length
+  // is known and arrive while q is prepared.  The block addresses use the
+  // length clamped into the cache, so they are valid whatever the step turns
+  // out to be.
   // ring > 0 (local-attention comparator): rows [0, ring) are a ring of the
   // ring most recent tokens, token t at row t mod ring; the new token
   // replaces the oldest, whose row is not attended
   const int n_raw = ring > 0 ? ring : kv_len[s];
   const int t_raw = cur_tok[s];
-  // the new row: thread tid < D takes element tid of k_new and v_new and
-  // the element k_new rotates against.  These vector loads go out before the
-  // block loads (the counter retires in issue order), so the new row is
-  // ready before the first block and its latency hides under the stream.
-  // Threads past D re-read element D - 1.
+  // the query and the new row: thread tid < D takes element tid of q, k_new
+  // and v_new, the elements q and k_new rotate against and their frequency
+  // (from the argument block).  These vector loads go out before the block
+  // loads (the counter retires in issue order), so they are ready before the
+  // first block.  Picking q and the frequency out of scalar registers instead
+  // cost about 1000 instructions a thread.  Threads past D re-read element
+  // D - 1.
   const int te = min(tid, D - 1);
   const int tp = te < HD ? te + HD : te - HD;
+  const uint16_t qx_raw = q[(int64_t)bh * D + te];
+  const uint16_t qp_raw = q[(int64_t)bh * D + tp];
+  const double freq = tab.w[min(te, tp)];
   const uint16_t kx_raw = k_new[(int64_t)bh * D + te];
   const uint16_t kp_raw = k_new[(int64_t)bh * D + tp];
   const uint16_t vx_raw = v_new[(int64_t)bh * D + te];
@@ -525,10 +581,6 @@ __global__ __launch_bounds__(NW * 64) void decode_mfma_kernel(
   // with SPEC2 (chosen by the host for caches large enough that slices are
   // taken to be long) the second block is issued before the length too
   if constexpr (FINAL && SPEC2) load_row(min(32 * (wave + NW) + kr, L_cap - 1), kB, vB);
-  const uint32_t* qw = reinterpret_cast<const uint32_t*>(q + (int64_t)bh * D);
-  uint32_t qword[HD];
-#pragma unroll
-  for (int j = 0; j < HD; ++j) qword[j] = qw[j];
   const bool t_ok = t_raw >= 0 && t_raw < L_meta;
   const int vu_t = t_ok ? vu[(int64_t)s * L_meta + t_raw] : 0;
   const int pos_t = (rotate && t_ok) ? pos[(int64_t)s * L_meta + t_raw] : 0;
@@ -536,7 +588,7 @@ __global__ __launch_bounds__(NW * 64) void decode_mfma_kernel(
   const int n = ring > 0 ? ring : min(max(n_raw, 0), L_cap - 1);
   const int slot = (ring > 0 && t_ok) ? t_raw % ring : -1;  // row of the new token (ring)
   const int rows = n + 1;
-  const ChunkPlan cp = chunk_plan(rows, ch);
+  const ChunkPlan cp = chunk_plan(rows, sp);
   const int r0 = chunk * cp.rows;
   const int r1 = min(r0 + cp.rows, rows);
   const int rc = min(r1, n);  // cache rows of this chunk: [r0, rc)
@@ -581,28 +633,19 @@ __global__ __launch_bounds__(NW * 64) void decode_mfma_kernel(
   }
   if (chunk >= cp.n) return;
 
-  // rotated q and k elements tid (tid < D), q from the words held in scalar
-  // registers; both turn by the same angle.  The key is rounded to bf16 as
-  // stored; its product with q and the value element go to LDS.
+  // rotated q and k elements tid (tid < D); both turn by the same angle.  The
+  // key is rounded to bf16 as stored; its product with q and the value
+  // element go to LDS.
   __shared__ float qs[D], kqs[D], vs[D];
   if (tid < D) {
-    uint32_t xw = 0, pw = 0;
-#pragma unroll
-    for (int j = 0; j < HD; ++j) {
-      xw = (tid >> 1) == j ? qword[j] : xw;
-      pw = (tp >> 1) == j ? qword[j] : pw;
-    }
-    float x = (tid & 1) ? bf16_hi(xw) : bf16_lo(xw);
+    float x = bf16_lo((uint32_t)qx_raw);
     float kx = bf16_lo((uint32_t)kx_raw);
     if (rotate) {
-      const float pv = (tp & 1) ? bf16_hi(pw) : bf16_lo(pw);
+      const float pv = bf16_lo((uint32_t)qp_raw);
       const float kp = bf16_lo((uint32_t)kp_raw);
-      double w = 0.0;
-#pragma unroll
-      for (int j = 0; j < HD; ++j) w = (tid % HD) == j ? tab.w[j] : w;
       const double two_pi = 6.283185307179586476925286766559;
       const double inv_two_pi = 0.15915494309189533576888376337251;
-      double ang = (double)pos_t * w;
+      double ang = (double)pos_t * freq;
       ang -= two_pi * rint(ang * inv_two_pi);
       float sn, cs;
       sincosf((float)ang, &sn, &cs);
@@ -641,9 +684,7 @@ __global__ __launch_bounds__(NW * 64) void decode_mfma_kernel(
   for (int a = 0; a < NA; ++a) acc[a] = 0.f;
   // takes a score (wave-uniform block maximum over lanes); returns its weight
   auto weigh = [&](float sc) {
-    float mb = sc;
-#pragma unroll
-    for (int off = 16; off > 0; off >>= 1) mb = fmaxf(mb, __shfl_xor(mb, off, 64));
+    const float mb = half_wave_max(sc);
     if (mb > M + DM_RESCALE) {
       const float f = exp2f(M - mb);  // 0 while M = -inf
       l *= f;
@@ -684,9 +725,7 @@ __global__ __launch_bounds__(NW * 64) void decode_mfma_kernel(
   if (holds_new && wave == 0) {
     float prod = kqs[lane];
     if (lane + 64 < D) prod += kqs[lane + 64];
-#pragma unroll
-    for (int off = 32; off > 0; off >>= 1) prod += __shfl_xor(prod, off, 64);
-    const float p = weigh(prod * qscale);
+    const float p = weigh(wave_sum(prod) * qscale);
     if (lane == 0) l += p;
     if (kr == 0) {
 #pragma unroll
@@ -717,8 +756,7 @@ __global__ __launch_bounds__(NW * 64) void decode_mfma_kernel(
   if (i + 2 * NW < nblk) compute(i + 2 * NW, kA, vA);
 
   // wave partials: l over the wave, values over each half-wave
-#pragma unroll
-  for (int off = 32; off > 0; off >>= 1) l += __shfl_xor(l, off, 64);
+  l = wave_sum(l);
   int base = 0;
   half_wave_reduce<NA, 16>(acc, lane, base);
   constexpr int NF = half_wave_count<NA, 16>();
@@ -731,7 +769,6 @@ __global__ __launch_bounds__(NW * 64) void decode_mfma_kernel(
   }
   if (lane == 0) { sm[wave] = M; sl[wave] = l; }
   __syncthreads();
-  __shared__ float res[D];
   if (tid < D) {
     float Mx = -INFINITY;
 #pragma unroll
@@ -739,26 +776,17 @@ __global__ __launch_bounds__(NW * 64) void decode_mfma_kernel(
     float Ls = 0.f, ov = 0.f;
 #pragma unroll
     for (int w = 0; w < NW; ++w) {
-      if (sm[w] == -INFINITY) continue;
       const float f = exp2f(sm[w] - Mx);
-      Ls += sl[w] * f;
-      ov += sacc[w][tid] * f;
+      const bool any = sm[w] != -INFINITY;  // the wave had a row
+      Ls += any ? sl[w] * f : 0.f;
+      ov += any ? sacc[w][tid] * f : 0.f;
     }
     if constexpr (FINAL) {
-      res[tid] = ov / Ls;
+      o[(int64_t)bh * D + tid] = f32_to_bf16(ov / Ls);
     } else {
       float* out = part + ((int64_t)bh * n_chunk_max + chunk) * (D + 2);
       out[2 + tid] = ov;
       if (tid == 0) { out[0] = Mx; out[1] = Ls; }
-    }
-  }
-  if constexpr (FINAL) {
-    __syncthreads();
-    if (tid < D / 8) {
-      float f[8];
-#pragma unroll
-      for (int e = 0; e < 8; ++e) f[e] = res[tid * 8 + e];
-      st16(o + (int64_t)bh * D + tid * 8, Piece<uint16_t>::pack(f));
     }
   }
 }
@@ -770,7 +798,8 @@ static int launch_decode(const void* q, const void* k_new, const void* v_new, vo
                          void* v_cache, const int32_t* kv_len, const int32_t* cur_tok,
                          const int32_t* vu, const int32_t* pos, int32_t L_meta, void* o,
                          int32_t b, int32_t H, int32_t L_cap, float scale, float theta,
-                         void* ws, int32_t* status, hipStream_t stream, int32_t ring = 0) {
+                         void* ws, size_t ws_bytes, int32_t* status, hipStream_t stream,
+                         int32_t ring = 0) {
   RopeTab tab;
   for (int i = 0; i < 40; ++i) tab.w[i] = 0.0;
   const int rotate = theta > 0.f ? 1 : 0;
@@ -785,14 +814,19 @@ static int launch_decode(const void* q, const void* k_new, const void* v_new, vo
   T* out = static_cast<T*>(o);
   const float qs = scale * LOG2E;
   const int slices = b * H;
-  if (slices >= DEC_SINGLE_MIN) {
+  const FastDiv by_H = make_div((uint32_t)H), by_slices = make_div((uint32_t)slices);
+  const bool one = sizeof(T) == 2 ? slices >= DEC_ONE_MIN ||
+                                        L_cap <= DEC_ONE_ROWS + DEC_ONE_ROWS_PER_SLICE * slices
+                                  : slices >= DEC_SINGLE_MIN;
+  if (one) {
     const bool narrow = slices >= DEC_NARROW_MIN;
     if constexpr (sizeof(T) == 2) {
       int cus = 0;
       const int rc = device_cus(&cus);
       if (rc) return rc;
       const int64_t slots = (int64_t)cus * 4 * DEC_WAVES_PER_SIMD;  // resident waves
-      const int nw = (int64_t)slices * 4 <= slots   ? 4
+      const int nw = (int64_t)slices * 8 <= slots && L_cap > DEC_EIGHT_ROWS ? 8
+                     : (int64_t)slices * 4 <= slots   ? 4
                      : (int64_t)slices * 2 <= slots ? 2
                      : slices <= slots              ? (D <= 64 ? 1 : 2)
                                                     : 4;
@@ -800,13 +834,14 @@ static int launch_decode(const void* q, const void* k_new, const void* v_new, vo
       // to hold long slices: both first blocks of every wave are then read
       // before the slice length arrives (rows past a shorter slice are read
       // for nothing, never used).
-      const bool spec2 = ring == 0 && (int64_t)L_cap >= (int64_t)DEC_SPEC2_ROWS * nw;
+      const bool spec2 = ring == 0 && nw < 8 && (int64_t)L_cap >= (int64_t)DEC_SPEC2_ROWS * nw;
 #define SCKV_DECODE_LAUNCH(DD, NWW, SP)                                                          \
   decode_mfma_kernel<DD, NWW, true, SP><<<slices, NWW * 64, 0, stream>>>(                         \
       qq, kn, vn, kc, vc, kv_len, cur_tok, vu, pos, L_meta, H, L_cap, qs, rotate, tab, part, 1,  \
-      slices, L_cap, out, status, ring)
+      by_H, by_slices, slices, Split{1, 1}, out, status, ring)
       constexpr int D1 = D <= 64 ? D : 64;  // nw == 1 only where D <= 64
-      if (nw == 1 && spec2) SCKV_DECODE_LAUNCH(D1, 1, true);
+      if (nw == 8) SCKV_DECODE_LAUNCH(D, 8, false);
+      else if (nw == 1 && spec2) SCKV_DECODE_LAUNCH(D1, 1, true);
       else if (nw == 1) SCKV_DECODE_LAUNCH(D1, 1, false);
       else if (nw == 2 && spec2) SCKV_DECODE_LAUNCH(D, 2, true);
       else if (nw == 2) SCKV_DECODE_LAUNCH(D, 2, false);
@@ -817,28 +852,33 @@ static int launch_decode(const void* q, const void* k_new, const void* v_new, vo
       if (narrow)
         decode_chunk_kernel<T, D, 256, true><<<slices, 256, 0, stream>>>(
             qq, kn, vn, kc, vc, kv_len, cur_tok, vu, pos, L_meta, H, L_cap, qs, rotate, tab, part,
-            1, slices, L_cap, out, status);
+            1, slices, Split{1, 1}, out, status);
       else
         decode_chunk_kernel<T, D, 512, true><<<slices, 512, 0, stream>>>(
             qq, kn, vn, kc, vc, kv_len, cur_tok, vu, pos, L_meta, H, L_cap, qs, rotate, tab, part,
-            1, slices, L_cap, out, status);
+            1, slices, Split{1, 1}, out, status);
     }
     return hip_check(hipGetLastError(), "compacted_decode_attn: launch");
   }
-  const int nc = n_chunks(L_cap);
+  // the caller's workspace holds at least n_chunks(L_cap) partials a slice
+  // (checked); a larger one lets a launch of few slices split them finer
+  const int fit = (int)std::min<size_t>(ws_bytes / ((size_t)slices * (D + 2) * sizeof(float)), 0x7fffffff);
+  const int want = std::max(1, DEC_FILL / slices);
+  const int nc = std::min(fit, std::max(n_chunks(L_cap), std::min(want, (L_cap + DEC_CH_MIN - 1) / DEC_CH_MIN)));
+  const Split sp{want, nc};
   const int n_work = slices * nc;
   if constexpr (sizeof(T) == 2)
     decode_mfma_kernel<D, 4, false><<<n_work, 256, 0, stream>>>(
         qq, kn, vn, kc, vc, kv_len, cur_tok, vu, pos, L_meta, H, L_cap, qs, rotate, tab, part, nc,
-        n_work, DEC_CH, out, status, ring);
+        by_H, by_slices, slices, sp, out, status, ring);
   else
     decode_chunk_kernel<T, D, DEC_THREADS, false><<<n_work, DEC_THREADS, 0, stream>>>(
         qq, kn, vn, kc, vc, kv_len, cur_tok, vu, pos, L_meta, H, L_cap, qs, rotate, tab, part, nc,
-        n_work, DEC_CH, out, status);
+        n_work, sp, out, status);
   int rc = hip_check(hipGetLastError(), "compacted_decode_attn: chunk launch");
   if (rc) return rc;
-  decode_combine_kernel<T, D><<<slices, 64, 0, stream>>>(vn, kv_len, cur_tok, vu, L_meta, H, L_cap,
-                                                          part, nc, DEC_CH, out, status, ring);
+  decode_combine_kernel<T, D><<<slices, 64 * COMBINE_WAVES, 0, stream>>>(
+      vn, kv_len, cur_tok, vu, L_meta, H, by_H, L_cap, part, nc, sp, out, status, ring);
   return hip_check(hipGetLastError(), "compacted_decode_attn: combine launch");
 }
 
@@ -879,8 +919,8 @@ extern "C" int local_decode_attn(const void* q, const void* k_new, const void* v
     return fail(SCKV_EINVAL, "local_decode_attn: buffers must be 16-byte aligned");
   const int32_t* p = pos ? pos : vu;
   return d_head == 64
-             ? launch_decode<uint16_t, 64>(q, k_new, v_new, k_cache, v_cache, nullptr, cur_tok, vu, p, L_meta, o, b, H, L_cap, scale, rope_theta, ws, status, stream, W)
-             : launch_decode<uint16_t, 80>(q, k_new, v_new, k_cache, v_cache, nullptr, cur_tok, vu, p, L_meta, o, b, H, L_cap, scale, rope_theta, ws, status, stream, W);
+             ? launch_decode<uint16_t, 64>(q, k_new, v_new, k_cache, v_cache, nullptr, cur_tok, vu, p, L_meta, o, b, H, L_cap, scale, rope_theta, ws, ws_bytes, status, stream, W)
+             : launch_decode<uint16_t, 80>(q, k_new, v_new, k_cache, v_cache, nullptr, cur_tok, vu, p, L_meta, o, b, H, L_cap, scale, rope_theta, ws, ws_bytes, status, stream, W);
 }
 
 // Host checks of compacted_decode_attn and its allocation-free variant
@@ -913,16 +953,16 @@ static int decode_dispatch(const void* q, const void* k_new, const void* v_new, 
                            void* v_cache, const int32_t* kv_len, const int32_t* cur_tok,
                            const int32_t* vu, const int32_t* pos, int32_t L_meta, void* o,
                            int32_t b, int32_t H, int32_t L_cap, int32_t d_head, sckv_dtype dt,
-                           float scale, float rope_theta, void* ws, int32_t* status,
-                           hipStream_t stream) {
+                           float scale, float rope_theta, void* ws, size_t ws_bytes,
+                           int32_t* status, hipStream_t stream) {
   const int32_t* p = pos ? pos : vu;  // pos is read only when rotating
   if (dt == SCKV_BF16)
     return d_head == 64
-               ? launch_decode<uint16_t, 64>(q, k_new, v_new, k_cache, v_cache, kv_len, cur_tok, vu, p, L_meta, o, b, H, L_cap, scale, rope_theta, ws, status, stream)
-               : launch_decode<uint16_t, 80>(q, k_new, v_new, k_cache, v_cache, kv_len, cur_tok, vu, p, L_meta, o, b, H, L_cap, scale, rope_theta, ws, status, stream);
+               ? launch_decode<uint16_t, 64>(q, k_new, v_new, k_cache, v_cache, kv_len, cur_tok, vu, p, L_meta, o, b, H, L_cap, scale, rope_theta, ws, ws_bytes, status, stream)
+               : launch_decode<uint16_t, 80>(q, k_new, v_new, k_cache, v_cache, kv_len, cur_tok, vu, p, L_meta, o, b, H, L_cap, scale, rope_theta, ws, ws_bytes, status, stream);
   return d_head == 64
-             ? launch_decode<float, 64>(q, k_new, v_new, k_cache, v_cache, kv_len, cur_tok, vu, p, L_meta, o, b, H, L_cap, scale, rope_theta, ws, status, stream)
-             : launch_decode<float, 80>(q, k_new, v_new, k_cache, v_cache, kv_len, cur_tok, vu, p, L_meta, o, b, H, L_cap, scale, rope_theta, ws, status, stream);
+             ? launch_decode<float, 64>(q, k_new, v_new, k_cache, v_cache, kv_len, cur_tok, vu, p, L_meta, o, b, H, L_cap, scale, rope_theta, ws, ws_bytes, status, stream)
+             : launch_decode<float, 80>(q, k_new, v_new, k_cache, v_cache, kv_len, cur_tok, vu, p, L_meta, o, b, H, L_cap, scale, rope_theta, ws, ws_bytes, status, stream);
 }
 
 extern "C" int compacted_decode_attn(const void* q, const void* k_new, const void* v_new,
@@ -942,7 +982,7 @@ extern "C" int compacted_decode_attn(const void* q, const void* k_new, const voi
     return fail(SCKV_EINVAL, "compacted_decode_attn: workspace too small");
   if (!aligned16(ws)) return fail(SCKV_EINVAL, "compacted_decode_attn: buffers must be 16-byte aligned");
   return decode_dispatch(q, k_new, v_new, k_cache, v_cache, kv_len, cur_tok, vu, pos, L_meta, o, b,
-                         H, L_cap, d_head, dt, scale, rope_theta, ws, status, stream);
+                         H, L_cap, d_head, dt, scale, rope_theta, ws, ws_bytes, status, stream);
 }
 
 // ---------------------------------------------------------------------------
@@ -1005,5 +1045,5 @@ extern "C" int compacted_decode_attn_noalloc(const void* q, const void* k_new, c
   rc = scratch_address(&ws);
   if (rc) return rc;
   return decode_dispatch(q, k_new, v_new, k_cache, v_cache, kv_len, cur_tok, vu, pos, L_meta, o, b,
-                         H, L_cap, d_head, dt, scale, rope_theta, ws, status, stream);
+                         H, L_cap, d_head, dt, scale, rope_theta, ws, need, status, stream);
 }

@@ -109,6 +109,64 @@ constexpr int DPP_QUAD_XOR1 = 0xb1;      // quad_perm [1,0,3,2]
 constexpr int DPP_QUAD_XOR2 = 0x4e;      // quad_perm [2,3,0,1]
 constexpr int DPP_ROW_MIRROR = 0x140;    // lane i <- lane 15-i within a row
 constexpr int DPP_ROW_HALF_MIRROR = 0x141;  // lane i <- lane 7-i within a half row
+constexpr int DPP_ROW_ROR8 = 0x128;      // lane i <- lane i^8 within a row
+
+// swaps a's odd rows of 16 lanes with b's even rows (rows 0..3 of the wave):
+// afterwards a holds {a0, b0, a2, b2} and b {a1, b1, a3, b3}
+__device__ __forceinline__ void swap_rows16(float& a, float& b) {
+  const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(a), __float_as_uint(b), false, false);
+  a = __uint_as_float(r[0]);
+  b = __uint_as_float(r[1]);
+}
+
+// maximum over each half-wave of 32 lanes; every lane gets it
+__device__ __forceinline__ float half_wave_max(float x) {
+  x = fmaxf(x, dpp_mov<DPP_QUAD_XOR1>(x));
+  x = fmaxf(x, dpp_mov<DPP_QUAD_XOR2>(x));
+  x = fmaxf(x, dpp_mov<DPP_ROW_HALF_MIRROR>(x));
+  x = fmaxf(x, dpp_mov<DPP_ROW_MIRROR>(x));
+  float y = x;
+  swap_rows16(x, y);
+  return fmaxf(x, y);
+}
+
+// maximum over the wave's 64 lanes; every lane gets it
+__device__ __forceinline__ float wave_max(float x) {
+  x = half_wave_max(x);
+  const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+  return fmaxf(__uint_as_float(r[0]), __uint_as_float(r[1]));
+}
+
+// sum over the wave's 64 lanes; every lane gets it
+__device__ __forceinline__ float wave_sum(float x) {
+  x += dpp_mov<DPP_QUAD_XOR1>(x);
+  x += dpp_mov<DPP_QUAD_XOR2>(x);
+  x += dpp_mov<DPP_ROW_HALF_MIRROR>(x);
+  x += dpp_mov<DPP_ROW_MIRROR>(x);
+  float y = x;
+  swap_rows16(x, y);
+  x += y;
+  const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+  return __uint_as_float(r[0]) + __uint_as_float(r[1]);
+}
+
+// n / d for 0 <= n < 2^31 and 1 <= d < 2^31 by a multiplication: with l the
+// least integer for which d <= 2^l, m = floor(2^32 (2^l - d) / d) + 1 gives
+// n / d = (floor(m n / 2^32) + n) >> l (Granlund and Montgomery, "Division by
+// Invariant Integers using Multiplication", 1994); the sum stays below 2^32
+struct FastDiv {
+  uint32_t m, l;
+};
+inline FastDiv make_div(uint32_t d) {
+  FastDiv f;
+  f.l = 0;
+  while (((uint64_t)1 << f.l) < d) ++f.l;
+  f.m = (uint32_t)((((((uint64_t)1 << f.l) - d) << 32) / d) + 1);
+  return f;
+}
+__device__ __forceinline__ int fast_div(int n, FastDiv f) {
+  return (int)((__umulhi(f.m, (uint32_t)n) + (uint32_t)n) >> f.l);
+}
 
 // sum over aligned groups of GRP lanes (8, 16 or 32); every lane gets the sum
 template <int GRP>

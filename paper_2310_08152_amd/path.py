@@ -86,6 +86,9 @@ class KVCache:
                     meta.L_meta, self.b, self.L_cap, self.status, stream=stream)
 
 
+DECODE_PARTIALS = 1024  # chunk partials a decode workspace holds at least
+
+
 class Workspace:
     """Device workspaces sized for a batch shape (block: the block size of
     block-wise prompt processing, if used)."""
@@ -93,7 +96,11 @@ class Workspace:
     def __init__(self, b: int, H: int, L: int, L_cap: int, d: int, device, block: int = 0):
         self.prefill = torch.empty(max(1, B.sckv_prefill_workspace_bytes(b, max(L, 1))),
                                    dtype=torch.uint8, device=device)
-        self.decode = torch.empty(max(1, B.sckv_decode_workspace_bytes(b, H, L_cap, d)),
+        # room for as many partials as a launch of few slices splits into
+        # (512 workgroups and a remainder), which is more than the least the
+        # library accepts where the cache is short
+        self.decode = torch.empty(max(1, B.sckv_decode_workspace_bytes(b, H, L_cap, d),
+                                      DECODE_PARTIALS * (d + 2) * 4),
                                   dtype=torch.uint8, device=device)
         self.prefill_cached = None
         if block > 0:

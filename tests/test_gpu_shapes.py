@@ -1,6 +1,6 @@
 """GPU launch shapes against the CPU oracle, at the sizes where a launch
 changes: counts of (sequence, head) slices around the multiples of 8 that the
-work order deals to the XCDs."""
+work order deals to the XCDs, and the split and one-workgroup decode."""
 import numpy as np
 import pytest
 import torch
@@ -57,3 +57,43 @@ def test_prefill_covers_every_slice(b, H):
     for s in range(b):
         ref = O.masked_attention(Q[s], K[s], V[s], O.attention_mask(O.token_types(spans[s], L)))
         assert np.abs(Og[s] - ref).max() <= TOL, s
+
+
+# (b, H, L_cap): split launches whose chunks are cut finer than 1024 rows (8,
+# 32, 96 slices), one workgroup per slice below 256 slices (a short cache) and
+# from there on, with eight waves (a cache above 2048 rows) and with four
+@pytest.mark.parametrize("finer", [True, False], ids=["room", "least"])
+@pytest.mark.parametrize("d,theta", [(64, 0.0), (80, 10000.0)])
+@pytest.mark.parametrize("b,H,L_cap", [(4, 2, 2400), (4, 8, 1400), (4, 24, 1500), (4, 16, 1000),
+                                       (4, 64, 2100), (4, 64, 1100), (4, 72, 1100)])
+def test_decode_launch_shapes(b, H, L_cap, d, theta, finer):
+    """One decode step against the oracle, at chunk edges, with the workspace
+    path.Workspace allocates and with the least one the library accepts."""
+    print(f"decode b={b} H={H} L_cap={L_cap} d={d} finer={finer}", flush=True)
+    from paper_2310_08152_amd import binding as B
+    lens = [0, 129, 1024, L_cap - 1] if L_cap > 1024 else [1, 127, 128, L_cap - 1]
+    T = L_cap + 8
+    meta = P().SpanMeta([[] for _ in range(b)], T, DEV)
+    cache = P().KVCache(1, b, H, L_cap, d, torch.bfloat16, DEV)
+    cache.kv.copy_(rnd(cache.kv.shape, 71))
+    cache.kv_len.copy_(torch.tensor(lens, dtype=torch.int32))
+    cache.cur_tok.copy_(torch.tensor(lens, dtype=torch.int32))
+    ws = P().Workspace(b, H, 1, L_cap, d, DEV)
+    if not finer:
+        ws.decode = ws.decode[:B.sckv_decode_workspace_bytes(b, H, L_cap, d)].contiguous()
+    q, kn, vn = (rnd((b, H, d), 72 + i) for i in range(3))
+    o = torch.full_like(q, float("nan"))
+    K, V = f64(cache.kv[0, 0]), f64(cache.kv[0, 1])
+    P().decode_layer(q, kn, vn, cache, 0, meta, ws, o, theta=theta)
+    torch.cuda.synchronize()
+    assert int(cache.status) == 0
+    Q, KN, VN, Og = f64(q), f64(kn), f64(vn), f64(o)
+    for s in range(b):
+        qs, ks = Q[s], KN[s]
+        if theta > 0:
+            qs, ks = (np.stack([O.rope_rotate_half(x[h][None], [lens[s]], theta)[0]
+                                for h in range(H)]) for x in (qs, ks))
+        ref = O.decode_attention(qs, ks, VN[s], K[s], V[s], lens[s], False)
+        # fp32 sums; the output's bf16 rounding, and the new key's
+        assert np.abs(Og[s] - ref).max() <= TOL, (s, np.abs(Og[s] - ref).max())
+        assert np.array_equal(f64(cache.kv[0, 1, s, :, lens[s]]), VN[s])
