@@ -103,60 +103,85 @@ __global__ __launch_bounds__(256) void prefill_plan_kernel(const int32_t* __rest
   }
   const int32_t* v = vu + (int64_t)s * L_meta;
   uint32_t* out = list + ((int64_t)s * n_qt + qt) * L_pad;
-  __shared__ int wave_cnt[4];
+  // PLAN_U columns a thread in flight together: the rounds follow one another
+  // and each costs a round trip to memory and two barriers (prompts of 4096
+  // tokens, 16 sequences: 18.2 us with one column a thread, 10.9 us with four)
+  constexpr int PLAN_U = 4;
+  __shared__ int cnt[PLAN_U * 4];  // listed columns of (pass u, wave w) at [4u + w]
   int carry = 0;
-  for (int base = 0; base < jend; base += 256) {
-    const int j = base + tid;
-    bool ok = false;
-    uint32_t e = 0;
-    if (j < jend) {
+  for (int base = 0; base < jend; base += 256 * PLAN_U) {
+    bool ok[PLAN_U];
+    uint32_t e[PLAN_U];
+    int tok[PLAN_U], x[PLAN_U];
+    uint64_t m[PLAN_U];
+#pragma unroll
+    for (int u = 0; u < PLAN_U; ++u) {
       // the column's token: the row itself, or the token a cache row holds
       // (a row whose token lies outside [0, L_meta) is never listed)
-      const int t = CACHED ? cc.tok[(int64_t)s * cc.L_cap + j] : j;
-      if (!CACHED || (t >= 0 && t < L_meta)) {
-        const int x = v[t];
-        ok = x >= I;
-        const int64_t rel = (int64_t)x - I;
-        e = (uint32_t)t | ((uint32_t)(rel > 255 ? 255 : rel) << 24);
+      const int j = base + u * 256 + tid;
+      ok[u] = j < jend;
+      tok[u] = CACHED ? (ok[u] ? cc.tok[(int64_t)s * cc.L_cap + j] : 0) : j;
+    }
+#pragma unroll
+    for (int u = 0; u < PLAN_U; ++u) {
+      if (CACHED) ok[u] = ok[u] && tok[u] >= 0 && tok[u] < L_meta;
+      x[u] = ok[u] ? v[tok[u]] : 0;
+    }
+#pragma unroll
+    for (int u = 0; u < PLAN_U; ++u) {
+      ok[u] = ok[u] && x[u] >= I;
+      const int64_t rel = (int64_t)x[u] - I;
+      e[u] = (uint32_t)tok[u] | ((uint32_t)(rel > 255 ? 255 : rel) << 24);
+      m[u] = __ballot(ok[u]);
+      if ((tid & 63) == 0) cnt[4 * u + wave] = __popcll(m[u]);
+    }
+    __syncthreads();
+    int sum = carry;
+#pragma unroll
+    for (int u = 0; u < PLAN_U; ++u) {
+      int off = 0;
+#pragma unroll
+      for (int w = 0; w < 4; ++w) {
+        if (w == wave) off = sum;
+        sum += cnt[4 * u + w];
+      }
+      if (ok[u]) {
+        out[off + mask_rank(m[u])] = e[u];
+        if constexpr (CACHED)
+          cc.rows[((int64_t)s * n_qt + qt) * L_pad + off + mask_rank(m[u])] = base + u * 256 + tid;
       }
     }
-    const uint64_t m = __ballot(ok);
-    if ((tid & 63) == 0) wave_cnt[wave] = __popcll(m);
-    __syncthreads();
-    int off = carry, total = 0;
-#pragma unroll
-    for (int w = 0; w < 4; ++w) {
-      const int c = wave_cnt[w];
-      if (w < wave) off += c;
-      total += c;
-    }
-    if (ok) {
-      out[off + mask_rank(m)] = e;
-      if constexpr (CACHED) cc.rows[((int64_t)s * n_qt + qt) * L_pad + off + mask_rank(m)] = j;
-    }
-    carry += total;
+    carry = sum;
     __syncthreads();
   }
   if (tid == 0) count[(int64_t)s * n_qt + qt] = carry;
 
   // tile summaries: wave w takes tiles w, w+4, ... of the list just written
   // (the barrier that ended the last round orders those writes before these
-  // reads)
+  // reads), two at a time
   const int lane = tid & 63;
   const uint32_t* rws = CACHED ? cc.rows + ((int64_t)s * n_qt + qt) * L_pad : nullptr;
   TileSum* sum = info + ((int64_t)s * n_qt + qt) * (L_pad / 64);
-  for (int t = wave; t * 64 < carry; t += 4) {
-    const int nvalid = min(64, carry - t * 64);
-    const bool in = lane < nvalid;
-    const uint32_t e = in ? out[t * 64 + lane] : PF_NONE;
-    int vr = in ? (int)(e >> 24) : 255;
+  for (int t0 = wave; t0 * 64 < carry; t0 += 8) {
+    uint32_t e[2];
+    int row[2];
 #pragma unroll
-    for (int off = 1; off < 64; off <<= 1) vr = min(vr, __shfl_xor(vr, off, 64));
-    const int jmin = __shfl((int)(e & 0x00ffffffu), 0, 64);
-    const int jmax = __shfl((int)(e & 0x00ffffffu), nvalid - 1, 64);
-    int pad = jmax;
-    if constexpr (CACHED) pad = __shfl(in ? (int)rws[t * 64 + lane] : 0, nvalid - 1, 64);
-    if (lane == 0) sum[t] = TileSum{jmin, jmax, vr | (nvalid << 8), pad};
+    for (int i = 0; i < 2; ++i) {
+      const int at = (t0 + 4 * i) * 64 + lane;
+      e[i] = at < carry ? out[at] : PF_NONE;
+      row[i] = CACHED && at < carry ? (int)rws[at] : 0;
+    }
+#pragma unroll
+    for (int i = 0; i < 2; ++i) {
+      const int t = t0 + 4 * i;
+      if (t * 64 >= carry) break;
+      const int nvalid = min(64, carry - t * 64);
+      const int vr = (int)-wave_max(-(float)(lane < nvalid ? (int)(e[i] >> 24) : 255));
+      const int jmin = __builtin_amdgcn_readlane((int)(e[i] & 0x00ffffffu), 0);
+      const int jmax = __builtin_amdgcn_readlane((int)(e[i] & 0x00ffffffu), nvalid - 1);
+      const int pad = CACHED ? __builtin_amdgcn_readlane(row[i], nvalid - 1) : jmax;
+      if (lane == 0) sum[t] = TileSum{jmin, jmax, vr | (nvalid << 8), pad};
+    }
   }
 }
 

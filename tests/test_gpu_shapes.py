@@ -1,6 +1,7 @@
 """GPU launch shapes against the CPU oracle, at the sizes where a launch
 changes: counts of (sequence, head) slices around the multiples of 8 that the
-work order deals to the XCDs, and the split and one-workgroup decode."""
+work order deals to the XCDs, the split and one-workgroup decode, and the
+rounds of the bookkeeping kernels."""
 import numpy as np
 import pytest
 import torch
@@ -97,3 +98,36 @@ def test_decode_launch_shapes(b, H, L_cap, d, theta, finer):
         # fp32 sums; the output's bf16 rounding, and the new key's
         assert np.abs(Og[s] - ref).max() <= TOL, (s, np.abs(Og[s] - ref).max())
         assert np.array_equal(f64(cache.kv[0, 1, s, :, lens[s]]), VN[s])
+
+
+@pytest.mark.parametrize("L", [1, 1023, 1025, 4096, 4097, 9000])
+def test_span_metadata_plan_and_scan_round_sizes(L):
+    """Span metadata, compaction indices and (through the attention's last
+    rows) the prompt's plan at the edges of their rounds (256 tokens a
+    workgroup, 1024 columns and 4096 rows a round)."""
+    print(f"meta, plan, scan L={L}", flush=True)
+    rng = np.random.default_rng(L)
+    spans = [W().spans_uniform_lengths(L, 0.5, 2, 25, rng) if L > 60 else [], [(0, L + 3)]]
+    T = L + 4
+    meta = P().SpanMeta(spans, T, DEV)
+    d, H = 64, 1
+    cache = P().KVCache(1, 2, H, L + 1, d, torch.bfloat16, DEV)
+    cache.kv.copy_(rnd(cache.kv.shape, 81))
+    cache.start_prompt(L, meta)
+    cache.compact(meta)
+    kept = cache.kept_src.cpu().numpy()
+    q, k, v = (rnd((2, H, L, d), 82 + i) for i in range(3))
+    o = torch.empty_like(q)
+    P().prefill_layer(q, k, v, o, meta, P().Workspace(2, H, L, 1, d, DEV), L)
+    torch.cuda.synchronize()
+    Og = f64(o)
+    rows = sorted({0, L // 2, max(0, L - 2), L - 1})
+    for s in range(2):
+        types = O.token_types(spans[s], T)
+        assert np.array_equal(meta.pos[s].cpu().numpy(), O.tie_positions(types)), s
+        keep = np.flatnonzero(O.keep_rows(types, L)[:L])
+        assert int(cache.kv_len[s]) == len(keep)
+        assert np.array_equal(kept[s, :len(keep)], keep) and (kept[s, len(keep):] == -1).all()
+        m = O.attention_mask_rows(O.token_types(spans[s], L), rows)
+        ref = O.masked_attention(f64(q)[s][:, rows], f64(k)[s], f64(v)[s], m)
+        assert np.abs(Og[s][:, rows] - ref).max() <= TOL, s
