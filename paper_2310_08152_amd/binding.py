@@ -6,6 +6,11 @@ pointers, sizes and the current HIP stream to the C entry point of the same
 name, and raises ``SckvError`` on a non-zero status.  No computation of the
 method happens here, and there is no fallback: if the library is missing the
 import fails.
+
+The calls that take device tensors first go to the native half of this module
+(csrc/bind.cpp), which makes the same checks and the call.  Where it cannot
+vouch for an argument it returns None and the checks written here decide: they
+raise, or make the call through ctypes.
 """
 from __future__ import annotations
 
@@ -126,7 +131,7 @@ def _avail(t) -> int:
     return t.untyped_storage().nbytes() // t.element_size() - t.storage_offset()
 
 
-_torch = _I32 = _FLOATS = _raw_stream = None
+_torch = _I32 = _FLOATS = _raw_stream = _native = None
 
 
 def _tm():
@@ -141,6 +146,30 @@ def _tm():
             lambda dev: torch.cuda.current_stream(dev).cuda_stream)
         _torch = torch
     return _torch
+
+
+def _nat():
+    """The native half, loaded on first use (it links against torch)."""
+    global _native
+    if _native is None:
+        _tm()
+        try:
+            from . import _bind
+        except ImportError as e:
+            raise ImportError("the native half of the binding (_bind.so) cannot be loaded: build "
+                              "it with `python -m paper_2310_08152_amd.build`") from e
+        _bind.init({n: ctypes.cast(getattr(lib, n), ctypes.c_void_p).value for n in _SIGS},
+                   _raw_stream)
+        _native = _bind
+    return _native
+
+
+def _done(rc) -> bool:
+    """Whether the native half made the call; raises if the library refused."""
+    if rc is None:
+        return False
+    _check(rc)
+    return True
 
 
 def _dev(t, what, kind=None, need=0, contiguous=False, nullable=False):
@@ -245,6 +274,9 @@ def sckv_span_meta(cl, cr, n, L_meta: int, spans_dev, vu, pos=None, stream=None)
 
 def rope_apply(x, y, b: int, H: int, n: int, x_stride_bh: int, y_stride_bh: int, d_head: int,
                pos, L_meta: int, tok0: int, theta: float, stream=None):
+    if _done((_native or _nat()).rope_apply(x, y, b, H, n, x_stride_bh, y_stride_bh, d_head, pos,
+        L_meta, tok0, theta, stream)):
+        return
     px = _rows(x, "x", b, H, n, d_head, x_stride_bh)
     py = _rows(y, "y", b, H, n, d_head, y_stride_bh, x.dtype)
     pp = _dev(pos, "pos", "i32", b * L_meta, True, nullable=theta == 0)
@@ -255,6 +287,9 @@ def rope_apply(x, y, b: int, H: int, n: int, x_stride_bh: int, y_stride_bh: int,
 def rope_apply_at(x, y, row0, y_rows: int, b: int, H: int, n: int, x_stride_bh: int,
                   y_stride_bh: int, d_head: int, pos, L_meta: int, tok0: int, theta: float,
                   status=None, stream=None):
+    if _done((_native or _nat()).rope_apply_at(x, y, row0, y_rows, b, H, n, x_stride_bh,
+        y_stride_bh, d_head, pos, L_meta, tok0, theta, status, stream)):
+        return
     px = _rows(x, "x", b, H, n, d_head, x_stride_bh)
     py = _rows(y, "y", b, H, y_rows, d_head, y_stride_bh, x.dtype)
     _check(lib.rope_apply_at(px, py, _dev(row0, "row0", "i32", b, True), y_rows, b, H, n,
@@ -285,6 +320,10 @@ def span_masked_prefill_attn_cached(q, k_cache, v_cache, o, b: int, H: int, nq: 
                                     q_stride_bh: int, kv_stride_bh: int, o_stride_bh: int,
                                     scale: float, vu, L_meta: int, tok0: int, row0, tok_idx,
                                     L_cap: int, ws, status=None, stream=None):
+    if _done((_native or _nat()).span_masked_prefill_attn_cached(q, k_cache, v_cache, o, b, H, nq,
+        d_head, q_stride_bh, kv_stride_bh, o_stride_bh, scale, vu, L_meta, tok0, row0, tok_idx,
+        L_cap, ws, status, stream)):
+        return
     pq, pk, pv, po, pvu, pr0, ptok, pw, nw, pst = _cached_args(
         q, k_cache, v_cache, o, b, H, nq, d_head, q_stride_bh, kv_stride_bh, o_stride_bh, vu,
         L_meta, row0, tok_idx, L_cap, ws, status)
@@ -295,6 +334,9 @@ def span_masked_prefill_attn_cached(q, k_cache, v_cache, o, b: int, H: int, nq: 
 
 def sckv_prefill_cached_plan(vu, L_meta: int, tok0: int, row0, tok_idx, L_cap: int, b: int,
                              nq: int, ws, stream=None):
+    if _done((_native or _nat()).sckv_prefill_cached_plan(vu, L_meta, tok0, row0, tok_idx, L_cap,
+        b, nq, ws, stream)):
+        return
     pw, nw = _ws(ws)
     _check(lib.sckv_prefill_cached_plan(_dev(vu, "vu", "i32", b * L_meta, True), L_meta, tok0,
                                         _dev(row0, "row0", "i32", b, True),
@@ -307,6 +349,10 @@ def span_masked_prefill_attn_cached_planned(q, k_cache, v_cache, o, b: int, H: i
                                             o_stride_bh: int, scale: float, vu, L_meta: int,
                                             tok0: int, row0, tok_idx, L_cap: int, ws, status=None,
                                             stream=None):
+    if _done((_native or _nat()).span_masked_prefill_attn_cached_planned(q, k_cache, v_cache, o, b,
+        H, nq, d_head, q_stride_bh, kv_stride_bh, o_stride_bh, scale, vu, L_meta, tok0, row0,
+        tok_idx, L_cap, ws, status, stream)):
+        return
     pq, pk, pv, po, pvu, pr0, ptok, pw, nw, pst = _cached_args(
         q, k_cache, v_cache, o, b, H, nq, d_head, q_stride_bh, kv_stride_bh, o_stride_bh, vu,
         L_meta, row0, tok_idx, L_cap, ws, status)
@@ -317,6 +363,9 @@ def span_masked_prefill_attn_cached_planned(q, k_cache, v_cache, o, b: int, H: i
 
 def kv_extend(kv_len, tok_idx, pos_ids, row0_out, pos, L_meta: int, tok0: int, n: int, b: int,
               L_cap: int, status=None, stream=None):
+    if _done((_native or _nat()).kv_extend(kv_len, tok_idx, pos_ids, row0_out, pos, L_meta, tok0,
+        n, b, L_cap, status, stream)):
+        return
     _check(lib.kv_extend(_dev(kv_len, "kv_len", "i32", b, True),
                          _dev(tok_idx, "tok_idx", "i32", b * L_cap, True),
                          _dev(pos_ids, "pos_ids", "i32", b * L_cap, True),
@@ -343,6 +392,9 @@ def _prefill_args(q, k, v, o, b, H, L, d_head, q_stride_bh, kv_stride_bh, o_stri
 def span_masked_prefill_attn(q, k, v, o, b: int, H: int, L: int, d_head: int, q_stride_bh: int,
                              kv_stride_bh: int, o_stride_bh: int, scale: float, vu, L_meta: int,
                              ws, stream=None):
+    if _done((_native or _nat()).span_masked_prefill_attn(q, k, v, o, b, H, L, d_head, q_stride_bh,
+        kv_stride_bh, o_stride_bh, scale, vu, L_meta, ws, stream)):
+        return
     pq, pk, pv, po, pvu, pw, nw = _prefill_args(q, k, v, o, b, H, L, d_head, q_stride_bh,
                                                 kv_stride_bh, o_stride_bh, vu, L_meta, ws)
     _check(lib.span_masked_prefill_attn(pq, pk, pv, po, b, H, L, d_head, q_stride_bh,
@@ -351,6 +403,8 @@ def span_masked_prefill_attn(q, k, v, o, b: int, H: int, L: int, d_head: int, q_
 
 
 def sckv_prefill_plan(vu, L_meta: int, b: int, L: int, ws, stream=None):
+    if _done((_native or _nat()).sckv_prefill_plan(vu, L_meta, b, L, ws, stream)):
+        return
     pw, nw = _ws(ws)
     _check(lib.sckv_prefill_plan(_dev(vu, "vu", "i32", b * L_meta, True), L_meta, b, L, pw, nw,
                                  _stream(stream, ws)))
@@ -359,6 +413,9 @@ def sckv_prefill_plan(vu, L_meta: int, b: int, L: int, ws, stream=None):
 def span_masked_prefill_attn_planned(q, k, v, o, b: int, H: int, L: int, d_head: int,
                                      q_stride_bh: int, kv_stride_bh: int, o_stride_bh: int,
                                      scale: float, vu, L_meta: int, ws, stream=None):
+    if _done((_native or _nat()).span_masked_prefill_attn_planned(q, k, v, o, b, H, L, d_head,
+        q_stride_bh, kv_stride_bh, o_stride_bh, scale, vu, L_meta, ws, stream)):
+        return
     pq, pk, pv, po, pvu, pw, nw = _prefill_args(q, k, v, o, b, H, L, d_head, q_stride_bh,
                                                 kv_stride_bh, o_stride_bh, vu, L_meta, ws)
     _check(lib.span_masked_prefill_attn_planned(pq, pk, pv, po, b, H, L, d_head, q_stride_bh,
@@ -368,6 +425,9 @@ def span_masked_prefill_attn_planned(q, k, v, o, b: int, H: int, L: int, d_head:
 
 def kv_compact(kv, kv_out, M: int, b: int, H: int, L_cap: int, d_head: int, kv_len, tok_idx,
                pos_ids, next_tok, vu, L_meta: int, kept_src_row, stream=None):
+    if _done((_native or _nat()).kv_compact(kv, kv_out, M, b, H, L_cap, d_head, kv_len, tok_idx,
+        pos_ids, next_tok, vu, L_meta, kept_src_row, stream)):
+        return
     n = M * 2 * b * H * L_cap * d_head
     pkv = _dev(kv, "kv", "float", n, True)
     pout = _dev(kv_out, "kv_out", "float", n, True, nullable=True)
@@ -410,6 +470,9 @@ def _decode_args(q, k_new, v_new, k_cache, v_cache, o, vu, pos, L_meta, b, H, L_
 def compacted_decode_attn(q, k_new, v_new, k_cache, v_cache, kv_len, cur_tok, vu, pos,
                           L_meta: int, o, b: int, H: int, L_cap: int, d_head: int, scale: float,
                           rope_theta: float, ws, status=None, stream=None):
+    if _done((_native or _nat()).compacted_decode_attn(q, k_new, v_new, k_cache, v_cache, kv_len,
+        cur_tok, vu, pos, L_meta, o, b, H, L_cap, d_head, scale, rope_theta, ws, status, stream)):
+        return
     pq, pkn, pvn, pkc, pvc, po, pvu, ppos, pst = _decode_args(
         q, k_new, v_new, k_cache, v_cache, o, vu, pos, L_meta, b, H, L_cap, d_head, rope_theta,
         status)
@@ -426,6 +489,10 @@ def compacted_decode_attn_noalloc(q, k_new, v_new, k_cache, v_cache, kv_len, cur
                                   scale: float, rope_theta: float, status=None, stream=None):
     """compacted_decode_attn with the library's own scratch array in place
     of a workspace (no allocation by the call)."""
+    if _done((_native or _nat()).compacted_decode_attn_noalloc(q, k_new, v_new, k_cache, v_cache,
+        kv_len, cur_tok, vu, pos, L_meta, o, b, H, L_cap, d_head, scale, rope_theta, status,
+        stream)):
+        return
     pq, pkn, pvn, pkc, pvc, po, pvu, ppos, pst = _decode_args(
         q, k_new, v_new, k_cache, v_cache, o, vu, pos, L_meta, b, H, L_cap, d_head, rope_theta,
         status)
@@ -441,6 +508,9 @@ NOALLOC_SCRATCH_BYTES = 16 << 20  # SCKV_NOALLOC_SCRATCH_BYTES in sckv.h
 
 def kv_commit(kv_len, tok_idx, pos_ids, cur_tok, vu, pos, L_meta: int, b: int, L_cap: int,
               status=None, stream=None):
+    if _done((_native or _nat()).kv_commit(kv_len, tok_idx, pos_ids, cur_tok, vu, pos, L_meta, b,
+        L_cap, status, stream)):
+        return
     _check(lib.kv_commit(_dev(kv_len, "kv_len", "i32", b, True),
                          _dev(tok_idx, "tok_idx", "i32", b * L_cap, True),
                          _dev(pos_ids, "pos_ids", "i32", b * L_cap, True),
@@ -454,6 +524,9 @@ def kv_commit(kv_len, tok_idx, pos_ids, cur_tok, vu, pos, L_meta: int, b: int, L
 def local_decode_attn(q, k_new, v_new, k_cache, v_cache, W: int, cur_tok, vu, pos, L_meta: int,
                       o, b: int, H: int, L_cap: int, d_head: int, scale: float, rope_theta: float,
                       ws, status=None, stream=None):
+    if _done((_native or _nat()).local_decode_attn(q, k_new, v_new, k_cache, v_cache, W, cur_tok,
+        vu, pos, L_meta, o, b, H, L_cap, d_head, scale, rope_theta, ws, status, stream)):
+        return
     pq, pkn, pvn, pkc, pvc, po, pvu, ppos, pst = _decode_args(
         q, k_new, v_new, k_cache, v_cache, o, vu, pos, L_meta, b, H, L_cap, d_head, rope_theta,
         status)
