@@ -53,6 +53,23 @@ constexpr int PF_THREADS = 64 * PF_WAVES;
 // heaviest first (a dispatch simulation over the two prompt shapes puts
 // groups of 8 within 3-6% of an ideal balance, against 9-18% for one slice)
 constexpr int PF_GROUP = 8;
+// Groups of four waves per workgroup (bf16), each with every NS-th key tile:
+// a launch of fewer workgroups than the chip holds leaves its SIMDs one wave
+// each, whose tiles follow one another.  The groups take the room of the
+// workgroups that are not there (d = 80: three, d = 64: four fit a CU; two
+// groups of d = 64 fit it twice).  Measured, one group and so (us a layer, 32
+// heads unless stated): 777 tokens 19.7 and 16.5 (d = 80, three), 18.4 and
+// 15.1 (d = 64, two; four 15.5), 8 heads of 2048 tokens (d = 64) 28.1 and 19.8
+// (four; two 21.6), 1500 tokens (384 workgroups, d = 64) 23.0 and 18.8 (two).
+// With more workgroups each waits for a whole CU: 1024 of d = 64 36.2 and 38.1
+// (two), 512 of d = 80 17.8 and 22.1 (4 sequences of 512 tokens, three).
+constexpr int PF_ONE_PER_CU = 256, PF_TWO_PER_CU = 512;
+constexpr int PF_LONG = 1536;  // list entries from which four groups have tiles enough
+static int prefill_groups(int d, int n_work, int L_pad) {
+  if (d == 80) return n_work <= PF_ONE_PER_CU ? 3 : 1;
+  if (n_work <= PF_ONE_PER_CU && L_pad >= PF_LONG) return 4;
+  return n_work <= PF_TWO_PER_CU ? 2 : 1;
+}
 constexpr uint32_t PF_NONE = 0x00ffffffu;  // list entry of a padding column
 constexpr float PF_LOG2E = 1.4426950408889634f;
 // The running maximum of a query row is only moved (and the accumulators
@@ -282,7 +299,10 @@ __device__ __forceinline__ void work_item(int x, int nbh, int n_qt, int* bh, int
 // ---------------------------------------------------------------------------
 // main kernel
 // ---------------------------------------------------------------------------
-template <typename T, int D, bool CACHED>
+// NS > 1 (bf16): NS groups of four waves share the workgroup's query rows and
+// take every NS-th tile each, with tile buffers of their own; their partial
+// outputs are merged through LDS at the end.
+template <typename T, int D, bool CACHED, int NS = 1>
 __device__ __forceinline__ void prefill_attn_body(
     const T* __restrict__ q, const T* __restrict__ k, const T* __restrict__ v, T* __restrict__ o,
     int32_t H, int32_t L, int64_t qs, int64_t kvs, int64_t os, float c2,
@@ -296,13 +316,18 @@ __device__ __forceinline__ void prefill_attn_body(
 
   // Separate objects per buffer: the compiler then knows that a
   // direct-to-LDS load into one buffer does not feed reads of the other.
-  __shared__ __align__(1024) char kbuf0[TL::KBYTES];
-  __shared__ __align__(1024) char vbuf0[TL::VBYTES];
-  __shared__ __align__(1024) char kbuf1[C::NBUF == 2 ? TL::KBYTES : 1024];
-  __shared__ __align__(1024) char vbuf1[C::NBUF == 2 ? TL::VBYTES : 1024];
-  __shared__ uint32_t ent_ring[PF_ER][PF_BK];
-  __shared__ int32_t row_ring[PF_ER][PF_BK];  // bare row index per entry
-  __shared__ TileInfo info_ring[PF_ER];
+  // With several groups the buffers of a group are found at run time: the
+  // copies are then written in assembly, out of the compiler's sight (dma_rows).
+  static_assert(NS == 1 || (BF && C::NBUF == 2), "groups are for bf16");
+  constexpr int TILEB = TL::KBYTES + TL::VBYTES;
+  __shared__ __align__(1024) char kbuf0_s[NS == 1 ? TL::KBYTES : 1];
+  __shared__ __align__(1024) char vbuf0_s[NS == 1 ? TL::VBYTES : 1];
+  __shared__ __align__(1024) char kbuf1_s[NS != 1 ? 1 : C::NBUF == 2 ? TL::KBYTES : 1024];
+  __shared__ __align__(1024) char vbuf1_s[NS != 1 ? 1 : C::NBUF == 2 ? TL::VBYTES : 1024];
+  __shared__ __align__(1024) char tiles[NS == 1 ? 1 : NS * 2 * TILEB];
+  __shared__ uint32_t ent_rings[NS][PF_ER][PF_BK];
+  __shared__ int32_t row_rings[NS][PF_ER][PF_BK];  // bare row index per entry
+  __shared__ TileInfo info_rings[NS][PF_ER];
 
   int bh, qt;
   work_item(blockIdx.x, n_work / n_qt, n_qt, &bh, &qt);
@@ -312,11 +337,20 @@ __device__ __forceinline__ void prefill_attn_body(
   const int I_loc = qt * PF_BQ;
   const int I = tok0 + I_loc;
 
-  const int tid = threadIdx.x;
+  // thread, wave and group; all but the group count within the group
+  const int grp = NS == 1 ? 0 : __builtin_amdgcn_readfirstlane((int)threadIdx.x / PF_THREADS);
+  const int tid = (int)threadIdx.x - grp * PF_THREADS;
   const int wave = tid >> 6;
   const int lane = tid & 63;
   const int l32 = lane & 31;
   const int g = lane >> 5;
+  char* const kbuf0 = NS == 1 ? kbuf0_s : tiles + grp * 2 * TILEB;
+  char* const vbuf0 = NS == 1 ? vbuf0_s : tiles + grp * 2 * TILEB + TL::KBYTES;
+  char* const kbuf1 = NS == 1 ? kbuf1_s : tiles + grp * 2 * TILEB + TILEB;
+  char* const vbuf1 = NS == 1 ? vbuf1_s : tiles + grp * 2 * TILEB + TILEB + TL::KBYTES;
+  auto& ent_ring = ent_rings[grp];
+  auto& row_ring = row_rings[grp];
+  auto& info_ring = info_rings[grp];
   const int Iw_loc = I_loc + wave * 32;
   const int Iw = I + wave * 32;
   const int qrow = Iw_loc + l32;  // local query row
@@ -334,8 +368,8 @@ __device__ __forceinline__ void prefill_attn_body(
     own_row0 = cc.row0[s];
     if (own_row0 < 0 || (int64_t)own_row0 + L > cc.L_cap) {
       // the block's rows are not in the cache: NaN outputs, nothing read
-      if (cc.status && tid == 0 && qt == 0 && (bh % H) == 0) atomicOr(cc.status, SCKV_STATUS_CAP);
-      if (wave_live && qrow < L) {
+      if (cc.status && threadIdx.x == 0 && qt == 0 && (bh % H) == 0) atomicOr(cc.status, SCKV_STATUS_CAP);
+      if (grp == 0 && wave_live && qrow < L) {
         T* orow = o + (int64_t)bh * os + (int64_t)qrow * D;
         for (int e = g; e < D; e += 2) {
           if constexpr (sizeof(T) == 2) orow[e] = (T)0x7fc0;
@@ -348,7 +382,9 @@ __device__ __forceinline__ void prefill_attn_body(
   // clamped into the list, so that a workspace holding no valid plan (a
   // caller's mistake with the planned entry point) reads nothing outside it
   const int n_vis = min(max(count[(int64_t)s * n_qt + qt], 0), L_pad);
-  const int nt = (n_vis + PF_BK - 1) / PF_BK;
+  const int nt_all = (n_vis + PF_BK - 1) / PF_BK;
+  // the group's tiles: its tile kt is the list's tile NS * kt + grp
+  const int nt = NS == 1 ? nt_all : (nt_all - grp + NS - 1) / NS;
 
   // Padding value rows/columns are written once and never again.  For bf16
   // with padding, V^T row D is all ones, so the PV MFMA also produces each
@@ -390,24 +426,6 @@ __device__ __forceinline__ void prefill_attn_body(
     }
   }
 
-  // A <CL> row's output is its own value row.  It is copied here, where its
-  // loads overlap the staging of the first tiles, rather than after the loop
-  // (the epilogue then writes only the other rows).
-  const bool is_cl = qrow < L && vu[(int64_t)s * L_meta + qtok] == qtok;
-  T* const orow = o + (int64_t)bh * os + (int64_t)qrow * D;
-  if (is_cl) {
-    const T* vrow = vb + (int64_t)(own_row0 + qrow) * D;
-#pragma unroll
-    for (int db = 0; db < NDB; ++db)
-#pragma unroll
-      for (int jj = 0; jj < 4; ++jj) {
-        const int d0 = db * 32 + 8 * jj + 4 * g;
-        if (d0 >= D) continue;
-        if constexpr (BF) *reinterpret_cast<u32x2*>(orow + d0) = *reinterpret_cast<const u32x2*>(vrow + d0);
-        else st16(orow + d0, ld16(vrow + d0));
-      }
-  }
-
   f32x16 oacc[NDB];
 #pragma unroll
   for (int db = 0; db < NDB; ++db)
@@ -427,16 +445,18 @@ __device__ __forceinline__ void prefill_attn_body(
     TileSum s;
   };
   Staged stg = {PF_NONE, 0, {0, 0, 0, 0}};
-  auto nvalid_of = [&](int kt) { return min(PF_BK, n_vis - kt * PF_BK); };
-  // The loads do not depend on the list's length (tile kt < max(nt, 2) lies
-  // inside the block's list of L_pad >= 128 entries), so the first tiles'
+  auto list_tile = [&](int kt) { return NS == 1 ? kt : NS * kt + grp; };
+  auto nvalid_of = [&](int kt) { return min(PF_BK, n_vis - list_tile(kt) * PF_BK); };
+  // The loads do not depend on the list's length (the list has room for at
+  // least two tiles, and later ones are clamped into it), so the first tiles'
   // loads need not wait for the count; the length masks them when stored.
   auto load_entries = [&](int kt, Staged& st) {
+    const int lt = NS == 1 ? kt : min(list_tile(kt), L_pad / PF_BK - 1);
     if (tid < PF_BK) {
-      st.e = ents[kt * PF_BK + tid];
-      if constexpr (CACHED) st.r = (int)rws[kt * PF_BK + tid];
+      st.e = ents[lt * PF_BK + tid];
+      if constexpr (CACHED) st.r = (int)rws[lt * PF_BK + tid];
     }
-    if (wave == 0) st.s = tsum[kt];
+    if (wave == 0) st.s = tsum[lt];
   };
   // wave 0 writes the ring slot of tile kt from the entries and the plan's
   // summary of the tile
@@ -448,7 +468,7 @@ __device__ __forceinline__ void prefill_attn_body(
     const int slot = kt % PF_ER;
     if (wave == 0) {
       const int vr_n = __builtin_amdgcn_readfirstlane(sreg.vr_n);
-      const int nvalid = vr_n >> 8;
+      const int nvalid = NS == 1 ? vr_n >> 8 : min(vr_n >> 8, nvalid_of(kt));
       ent_ring[slot][lane] = ereg;
       // a padding row of the tile repeats the last valid row (its score is
       // masked, so any finite row will do)
@@ -506,6 +526,27 @@ __device__ __forceinline__ void prefill_attn_body(
     // must not be overwritten; without them (D = 64) every slot is data
     v_off[rnd] = sg < TL::PPR ? vpiece * 16 : -1;
   }
+  // A copy in assembly has no register results; wait_vmem and the step's
+  // barrier order it.  (Through the builtin, the compiler makes every LDS read
+  // wait for every copy where it cannot tell the buffers apart.)
+  typedef uint32_t rsrc_t __attribute__((ext_vector_type(4)));
+  auto rsrc_words = [&](const void* base) {
+    const uint64_t a = reinterpret_cast<uint64_t>(base);
+    return rsrc_t{(uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)a),
+                  (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(a >> 32)) & 0xffffu,
+                  (uint32_t)__builtin_amdgcn_readfirstlane(slice_bytes), 0x00020000u};
+  };
+  const rsrc_t krw = rsrc_words(kb), vrw = rsrc_words(vb);
+  auto copy_rows = [&](const __amdgpu_buffer_rsrc_t& rs, const rsrc_t& rw, char* dst, int off) {
+    if constexpr (NS == 1) {
+      __builtin_amdgcn_raw_ptr_buffer_load_lds(rs, (lds_ptr_t)dst, 16, off, 0, 0, 0);
+    } else {
+      const uint32_t lds = (uint32_t)__builtin_amdgcn_readfirstlane(
+          (int)(uint32_t)(uintptr_t)(__attribute__((address_space(3))) char*)dst);
+      asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, 0 offen lds"
+                   :: "s"(lds), "v"(off), "s"(rw) : "m0", "memory");
+    }
+  };
   auto dma_rows = [&](int kt, char* kdst, char* vdst) {
     const int32_t* rows = row_ring[kt % PF_ER];
     int kj[KRND], vj[VRND];
@@ -517,15 +558,13 @@ __device__ __forceinline__ void prefill_attn_body(
     for (int rnd = 0; rnd < KRND; ++rnd) {
       const int blk = rnd * PF_WAVES + wave_s;
       if (blk < TL::KSLOT)
-        __builtin_amdgcn_raw_ptr_buffer_load_lds(krs, (lds_ptr_t)(kdst + blk * 1024), 16,
-                                                 kj[rnd] * ROWB + k_off[rnd], 0, 0, 0);
+        copy_rows(krs, krw, kdst + blk * 1024, kj[rnd] * ROWB + k_off[rnd]);
     }
 #pragma unroll
     for (int rnd = 0; rnd < VRND; ++rnd) {
       const int blk = rnd * PF_WAVES + wave_s;
       if (blk < TL::VSLOT && (TL::VSLOT == TL::PPR || v_off[rnd] >= 0))
-        __builtin_amdgcn_raw_ptr_buffer_load_lds(vrs, (lds_ptr_t)(vdst + blk * 1024), 16,
-                                                 vj[rnd] * ROWB + v_off[rnd], 0, 0, 0);
+        copy_rows(vrs, vrw, vdst + blk * 1024, vj[rnd] * ROWB + v_off[rnd]);
     }
   };
 
@@ -697,7 +736,7 @@ __device__ __forceinline__ void prefill_attn_body(
       if (kt + 1 < nt) dma_rows(kt + 1, kn, vn);
     }
     if (kt + 2 < nt) load_entries(kt + 2, stg);
-    compute(kt, kc, vc);
+    if (NS == 1 || kt < nt) compute(kt, kc, vc);
     if (kt + 1 < nt) tcur = info_ring[(kt + 1) % PF_ER];
     if constexpr (C::NBUF == 1) {
       __syncthreads();
@@ -714,22 +753,88 @@ __device__ __forceinline__ void prefill_attn_body(
     Staged st1 = {PF_NONE, 0, {0, 0, 0, 0}};
     load_entries(0, stg);
     load_entries(1, st1);
-    store_entries(0, stg);
+    if (NS == 1 || nt > 0) store_entries(0, stg);
     if (nt > 1) store_entries(1, st1);
   }
   __syncthreads();
-  dma_rows(0, kbuf0, vbuf0);
+  if (NS == 1 || nt > 0) dma_rows(0, kbuf0, vbuf0);
+
+  // A <CL> row's output is its own value row.  It is copied here, while the
+  // first tile's rows are on their way: before the staging its two dependent
+  // loads would hold the first copies up, after the loop nothing hides them.
+  const bool is_cl = qrow < L && vu[(int64_t)s * L_meta + qtok] == qtok;
+  T* const orow = o + (int64_t)bh * os + (int64_t)qrow * D;
+  if (is_cl && grp == 0) {
+    const T* vrow = vb + (int64_t)(own_row0 + qrow) * D;
+#pragma unroll
+    for (int db = 0; db < NDB; ++db)
+#pragma unroll
+      for (int jj = 0; jj < 4; ++jj) {
+        const int d0 = db * 32 + 8 * jj + 4 * g;
+        if (d0 >= D) continue;
+        if constexpr (BF) *reinterpret_cast<u32x2*>(orow + d0) = *reinterpret_cast<const u32x2*>(vrow + d0);
+        else st16(orow + d0, ld16(vrow + d0));
+      }
+  }
+
   wait_vmem();
   __syncthreads();
   tcur = info_ring[0];
 
-  for (int kt = 0; kt < nt; kt += 2) {
+  // every group takes as many steps as the first, which has the most tiles
+  // (the barriers are the workgroup's)
+  const int steps = NS == 1 ? nt : (nt_all + NS - 1) / NS;
+  for (int kt = 0; kt < steps; kt += 2) {
     if constexpr (C::NBUF == 2) {
       iteration(kt, kbuf0, vbuf0, kbuf1, vbuf1);
-      if (kt + 1 < nt) iteration(kt + 1, kbuf1, vbuf1, kbuf0, vbuf0);
+      if (kt + 1 < steps) iteration(kt + 1, kbuf1, vbuf1, kbuf0, vbuf0);
     } else {
       iteration(kt, kbuf0, vbuf0, kbuf0, vbuf0);
       if (kt + 1 < nt) iteration(kt + 1, kbuf0, vbuf0, kbuf0, vbuf0);
+    }
+  }
+
+  // ---- the groups' outputs to the first group: a wave's accumulators go
+  // through LDS (the tile buffers are free) register by register ----
+  if constexpr (NS > 1) {
+    constexpr int NR = 16 * NDB + 2;  // accumulators, running maximum, sum
+    static_assert((NS - 1) * PF_WAVES * NR * 256 <= (int)sizeof(tiles), "room for the partials");
+    auto slot = [&](int gi) {
+      return reinterpret_cast<float*>(tiles) + ((gi - 1) * PF_WAVES + wave) * NR * 64 + lane;
+    };
+    if (grp > 0) {
+      float* w = slot(grp);
+#pragma unroll
+      for (int db = 0; db < NDB; ++db)
+#pragma unroll
+        for (int i = 0; i < 16; ++i) w[(db * 16 + i) * 64] = oacc[db][i];
+      w[16 * NDB * 64] = m_run;
+      w[(16 * NDB + 1) * 64] = lacc[0];
+    }
+    __syncthreads();
+    if (grp > 0) return;
+    float mg[NS], mx = m_run;
+#pragma unroll
+    for (int gi = 1; gi < NS; ++gi) {
+      mg[gi] = slot(gi)[16 * NDB * 64];
+      mx = fmaxf(mx, mg[gi]);
+    }
+    // a group without a visible tile for the row has weight 0 (and zeros)
+    const float f0 = fast_exp2(m_run - mx);
+    lacc[0] *= f0;
+#pragma unroll
+    for (int db = 0; db < NDB; ++db)
+#pragma unroll
+      for (int i = 0; i < 16; ++i) oacc[db][i] *= f0;
+#pragma unroll
+    for (int gi = 1; gi < NS; ++gi) {
+      const float f = fast_exp2(mg[gi] - mx);
+      const float* w = slot(gi);
+      lacc[0] = fmaf(w[(16 * NDB + 1) * 64], f, lacc[0]);
+#pragma unroll
+      for (int db = 0; db < NDB; ++db)
+#pragma unroll
+        for (int i = 0; i < 16; ++i) oacc[db][i] = fmaf(w[(db * 16 + i) * 64], f, oacc[db][i]);
     }
   }
 
@@ -778,14 +883,14 @@ __device__ __forceinline__ void prefill_attn_body(
 // of LDS per workgroup, so four workgroups share a CU) and at three at D = 80
 // (at most 168 registers; 49 KB of LDS), each measured faster than one wave
 // fewer; the fp32 variant (small parity cases) is not capped.
-template <int D, bool CACHED>
-__global__ __launch_bounds__(PF_THREADS) __attribute__((amdgpu_waves_per_eu(D == 64 ? 4 : 3))) void prefill_attn_kernel_bf16(
+template <int D, bool CACHED, int NS>
+__global__ __launch_bounds__(PF_THREADS * NS) __attribute__((amdgpu_waves_per_eu(D == 64 ? 4 : 3))) void prefill_attn_kernel_bf16(
     const uint16_t* __restrict__ q, const uint16_t* __restrict__ k, const uint16_t* __restrict__ v,
     uint16_t* __restrict__ o, int32_t H, int32_t L, int64_t qs, int64_t kvs, int64_t os, float c2,
     const int32_t* __restrict__ vu, int32_t L_meta, const uint32_t* __restrict__ list,
     const int32_t* __restrict__ count, const TileSum* __restrict__ info, int32_t n_qt,
     int32_t L_pad, int32_t n_work, PfCached cc) {
-  prefill_attn_body<uint16_t, D, CACHED>(q, k, v, o, H, L, qs, kvs, os, c2, vu, L_meta, list,
+  prefill_attn_body<uint16_t, D, CACHED, NS>(q, k, v, o, H, L, qs, kvs, os, c2, vu, L_meta, list,
                                          count, info, n_qt, L_pad, n_work, cc);
 }
 
@@ -813,12 +918,20 @@ static int launch_prefill(const void* q, const void* k, const void* v, void* o, 
     if (rc) return rc;
   }
   const int n_work = b * H * n_qt;
-  if constexpr (sizeof(T) == 2)
-    prefill_attn_kernel_bf16<D, CACHED><<<n_work, PF_THREADS, 0, stream>>>(
+  if constexpr (sizeof(T) == 2) {
+    const int groups = prefill_groups(D, n_work, L_pad);
+    auto kernel = prefill_attn_kernel_bf16<D, CACHED, 1>;
+    if constexpr (D == 64) {
+      if (groups == 2) kernel = prefill_attn_kernel_bf16<D, CACHED, 2>;
+      if (groups == 4) kernel = prefill_attn_kernel_bf16<D, CACHED, 4>;
+    } else {
+      if (groups == 3) kernel = prefill_attn_kernel_bf16<D, CACHED, 3>;
+    }
+    kernel<<<n_work, PF_THREADS * groups, 0, stream>>>(
         static_cast<const T*>(q), static_cast<const T*>(k), static_cast<const T*>(v),
         static_cast<T*>(o), H, L, qs, kvs, os, scale * PF_LOG2E, vu, L_meta, list, count, info,
         n_qt, L_pad, n_work, cc);
-  else
+  } else
     prefill_attn_kernel_f32<D, CACHED><<<n_work, PF_THREADS, 0, stream>>>(
         static_cast<const T*>(q), static_cast<const T*>(k), static_cast<const T*>(v),
         static_cast<T*>(o), H, L, qs, kvs, os, scale * PF_LOG2E, vu, L_meta, list, count, info,

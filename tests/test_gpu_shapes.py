@@ -131,3 +131,25 @@ def test_span_metadata_plan_and_scan_round_sizes(L):
         m = O.attention_mask_rows(O.token_types(spans[s], L), rows)
         ref = O.masked_attention(f64(q)[s][:, rows], f64(k)[s], f64(v)[s], m)
         assert np.abs(Og[s][:, rows] - ref).max() <= TOL, s
+
+
+# one workgroup's tiles shared among groups of waves (few workgroups: three
+# groups at d = 80, two or, for long lists, four at d = 64), with fewer tiles
+# than groups, as many, and a remainder; and one group (many workgroups)
+@pytest.mark.parametrize("d,H,L", [(80, 2, 1), (80, 2, 64), (80, 2, 130), (80, 2, 400), (80, 3, 901),
+                                   (64, 2, 1), (64, 2, 65), (64, 2, 700), (64, 2, 1600),
+                                   (80, 140, 129), (64, 260, 129), (80, 48, 700), (64, 96, 700)])
+def test_prefill_wave_groups(d, H, L):
+    print(f"prefill d={d} H={H} L={L}", flush=True)
+    rng = np.random.default_rng(L + d)
+    spans = [W().spans_uniform_lengths(L, 0.4, 4, 40, rng) if L > 60 else []]
+    q, k, v = (rnd((1, H, L, d), 300 + i) for i in range(3))
+    k[:, :, L // 2] *= 8  # one key whose scores jump: the running maxima of the groups differ
+    o = torch.full_like(q, float("nan"))
+    P().prefill_layer(q, k, v, o, P().SpanMeta(spans, L, DEV), P().Workspace(1, H, L, 1, d, DEV), L)
+    torch.cuda.synchronize()
+    heads = sorted({0, 1, H // 2, H - 1})
+    Q, K, V, Og = (f64(x)[0][heads] for x in (q, k, v, o))
+    assert np.isfinite(f64(o)).all()
+    ref = O.masked_attention(Q, K, V, O.attention_mask(O.token_types(spans[0], L)))
+    assert np.abs(Og - ref).max() <= TOL, np.abs(Og - ref).max()
