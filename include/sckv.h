@@ -147,6 +147,20 @@ int rope_apply_at(const void* x, void* y, const int32_t* row0, int32_t y_rows, i
                   int32_t* status, hipStream_t stream);
 
 /* ---------------------------------------------------------------------------
+ * One layer's block of a long prompt in one launch:
+ *   rope_apply_at(k -> k_cache, theta), rope_apply_at(v -> v_cache, 0) and
+ *   rope_apply(q -> qr, theta),
+ * with the same arguments, errors and status (Section 3, "Manipulating
+ * Key-Value Memory").  The buffers must not overlap.
+ * ------------------------------------------------------------------------- */
+int rope_block(const void* q, const void* k, const void* v, void* qr, void* k_cache,
+               void* v_cache, const int32_t* row0, int32_t L_cap, int32_t b, int32_t H, int32_t n,
+               int64_t q_stride_bh, int64_t k_stride_bh, int64_t v_stride_bh,
+               int64_t qr_stride_bh, int64_t cache_stride_bh, int32_t d_head, sckv_dtype dt,
+               const int32_t* pos, int32_t L_meta, int32_t tok0, float theta, int32_t* status,
+               hipStream_t stream);
+
+/* ---------------------------------------------------------------------------
  * Causal attention under the <CL>/<CR> span-exclusion mask (prefill).
  * Paper: Section 1 (tokens after <CR> do not see the enclosed tokens) and
  * Section 3.1 (<CL> sees only itself; normal tokens see earlier <CR> and
@@ -388,6 +402,16 @@ int local_decode_attn(const void* q, const void* k_new, const void* v_new, void*
 int kv_extend(int32_t* kv_len, int32_t* tok_idx, int32_t* pos_ids, int32_t* row0_out,
               const int32_t* pos, int32_t L_meta, int32_t tok0, int32_t n, int32_t b,
               int32_t L_cap, int32_t* status, hipStream_t stream);
+
+/* ---------------------------------------------------------------------------
+ * Bookkeeping of a whole prompt written to the cache's first rows: for each
+ * sequence, rows i < n get tok_idx = i and pos_ids = pos[s][i], and kv_len[s]
+ * = cur_tok[s] = n (0 < n <= L_cap, L_meta).
+ * Paper: Section 2 (cache layout).
+ * ------------------------------------------------------------------------- */
+int kv_start(int32_t* kv_len, int32_t* tok_idx, int32_t* pos_ids, int32_t* cur_tok,
+             const int32_t* pos, int32_t L_meta, int32_t n, int32_t b, int32_t L_cap,
+             hipStream_t stream);
 
 /* ---------------------------------------------------------------------------
  * Close a decode step after all layers: for each sequence, unless its current

@@ -57,6 +57,10 @@ _SIGS = {
                                   _i32, _i32, _f32, _p]),
     "rope_apply_at": (ctypes.c_int, [_p, _p, _p, _i32, _i32, _i32, _i32, _i64, _i64, _i32,
                                      ctypes.c_int, _p, _i32, _i32, _f32, _p, _p]),
+    "rope_block": (ctypes.c_int, [_p, _p, _p, _p, _p, _p, _p, _i32, _i32, _i32, _i32, _i64, _i64,
+                                  _i64, _i64, _i64, _i32, ctypes.c_int, _p, _i32, _i32, _f32, _p,
+                                  _p]),
+    "kv_start": (ctypes.c_int, [_p, _p, _p, _p, _p, _i32, _i32, _i32, _i32, _p]),
     "sckv_prefill_workspace_bytes": (_sz, [_i32, _i32]),
     "sckv_prefill_cached_workspace_bytes": (_sz, [_i32, _i32, _i32]),
     "span_masked_prefill_attn_cached": (ctypes.c_int, [_p, _p, _p, _p, _i32, _i32, _i32, _i32,
@@ -298,6 +302,42 @@ def rope_apply_at(x, y, row0, y_rows: int, b: int, H: int, n: int, x_stride_bh: 
                              L_meta, tok0, theta,
                              _dev(status, "status", "i32", 1, nullable=True),
                              _stream(stream, x)))
+
+
+def rope_block(q, k, v, qr, k_cache, v_cache, row0, L_cap: int, b: int, H: int, n: int,
+               q_stride_bh: int, k_stride_bh: int, v_stride_bh: int, qr_stride_bh: int,
+               cache_stride_bh: int, d_head: int, pos, L_meta: int, tok0: int, theta: float,
+               status=None, stream=None):
+    if _done((_native or _nat()).rope_block(q, k, v, qr, k_cache, v_cache, row0, L_cap, b, H, n,
+                                            q_stride_bh, k_stride_bh, v_stride_bh, qr_stride_bh,
+                                            cache_stride_bh, d_head, pos, L_meta, tok0, theta,
+                                            status, stream)):
+        return
+    pq = _rows(q, "q", b, H, n, d_head, q_stride_bh)
+    pk = _rows(k, "k", b, H, n, d_head, k_stride_bh, q.dtype)
+    pv = _rows(v, "v", b, H, n, d_head, v_stride_bh, q.dtype)
+    pr = _rows(qr, "qr", b, H, n, d_head, qr_stride_bh, q.dtype)
+    pkc = _rows(k_cache, "k_cache", b, H, L_cap, d_head, cache_stride_bh, q.dtype)
+    pvc = _rows(v_cache, "v_cache", b, H, L_cap, d_head, cache_stride_bh, q.dtype)
+    _check(lib.rope_block(pq, pk, pv, pr, pkc, pvc, _dev(row0, "row0", "i32", b, True), L_cap, b,
+                          H, n, q_stride_bh, k_stride_bh, v_stride_bh, qr_stride_bh,
+                          cache_stride_bh, d_head, _dtype_code(q),
+                          _dev(pos, "pos", "i32", b * L_meta, True, nullable=theta == 0), L_meta,
+                          tok0, theta, _dev(status, "status", "i32", 1, nullable=True),
+                          _stream(stream, q)))
+
+
+def kv_start(kv_len, tok_idx, pos_ids, cur_tok, pos, L_meta: int, n: int, b: int, L_cap: int,
+             stream=None):
+    if _done((_native or _nat()).kv_start(kv_len, tok_idx, pos_ids, cur_tok, pos, L_meta, n, b,
+                                          L_cap, stream)):
+        return
+    _check(lib.kv_start(_dev(kv_len, "kv_len", "i32", b, True),
+                        _dev(tok_idx, "tok_idx", "i32", b * L_cap, True),
+                        _dev(pos_ids, "pos_ids", "i32", b * L_cap, True),
+                        _dev(cur_tok, "cur_tok", "i32", b, True),
+                        _dev(pos, "pos", "i32", b * L_meta, True), L_meta, n, b, L_cap,
+                        _stream(stream, kv_len)))
 
 
 def sckv_prefill_cached_workspace_bytes(b: int, nq: int, L_cap: int) -> int:

@@ -25,7 +25,8 @@ PyObject* g_raw_stream = nullptr;  // device index -> the current stream's handl
 #define ENTRY(name) decltype(&::name) p_##name = nullptr;
 #define ENTRIES(X)                                                                               \
   X(compacted_decode_attn) X(compacted_decode_attn_noalloc) X(local_decode_attn) X(kv_commit)    \
-  X(kv_extend) X(kv_compact) X(rope_apply) X(rope_apply_at) X(span_masked_prefill_attn)          \
+  X(kv_extend) X(kv_start) X(kv_compact) X(rope_apply) X(rope_apply_at) X(rope_block)            \
+  X(span_masked_prefill_attn)                                                                    \
   X(span_masked_prefill_attn_planned) X(span_masked_prefill_attn_cached)                         \
   X(span_masked_prefill_attn_cached_planned) X(sckv_prefill_plan) X(sckv_prefill_cached_plan)
 ENTRIES(ENTRY)
@@ -296,6 +297,45 @@ PyObject* rope(PyObject* const* a, Py_ssize_t n) {
   });
 }
 
+PyObject* block(PyObject* const* a, Py_ssize_t n) {
+  Args g(a, n, 23);
+  const at::Tensor *q = g.tensor(), *k = g.tensor(), *v = g.tensor(), *qr = g.tensor(),
+                   *kc = g.tensor(), *vc = g.tensor(), *row0 = g.tensor();
+  const int32_t L_cap = g.i32(), b = g.i32(), H = g.i32(), rows_ = g.i32();
+  const int64_t qs = g.i64(), ks = g.i64(), vs = g.i64(), qrs = g.i64(), cs = g.i64();
+  const int32_t d = g.i32();
+  const at::Tensor* pos = g.tensor();
+  const int32_t L_meta = g.i32(), tok0 = g.i32();
+  const float theta = g.f32();
+  const at::Tensor* st = g.tensor();
+  if (!q) throw Defer();
+  const sckv_dtype dt = type_code(*q);
+  void *pq = rows(q, b, H, rows_, d, qs, dt), *pk = rows(k, b, H, rows_, d, ks, dt),
+       *pv = rows(v, b, H, rows_, d, vs, dt), *pr = rows(qr, b, H, rows_, d, qrs, dt),
+       *pkc = rows(kc, b, H, L_cap, d, cs, dt), *pvc = rows(vc, b, H, L_cap, d, cs, dt);
+  const int32_t *ppos = ints(pos, times({b, L_meta}), theta == 0.f), *prow = ints(row0, b);
+  int32_t* pst = word(st);
+  const hipStream_t stream = g.stream(q);
+  return status_of([&] {
+    return p_rope_block(pq, pk, pv, pr, pkc, pvc, prow, L_cap, b, H, rows_, qs, ks, vs, qrs, cs, d,
+                        dt, ppos, L_meta, tok0, theta, pst, stream);
+  });
+}
+
+PyObject* start(PyObject* const* a, Py_ssize_t n) {
+  Args g(a, n, 10);
+  const at::Tensor *len = g.tensor(), *tok = g.tensor(), *ids = g.tensor(), *cur = g.tensor(),
+                   *pos = g.tensor();
+  const int32_t L_meta = g.i32(), rows_ = g.i32(), b = g.i32(), L_cap = g.i32();
+  const int64_t nc = times({b, L_cap});
+  int32_t *plen = ints(len, b), *ptok = ints(tok, nc), *pids = ints(ids, nc), *pcur = ints(cur, b),
+          *ppos = ints(pos, times({b, L_meta}));
+  const hipStream_t stream = g.stream(len);
+  return status_of([&] {
+    return p_kv_start(plen, ptok, pids, pcur, ppos, L_meta, rows_, b, L_cap, stream);
+  });
+}
+
 template <bool PLANNED>
 PyObject* prefill(PyObject* const* a, Py_ssize_t n) {
   Args g(a, n, 16);
@@ -418,9 +458,11 @@ PyMethodDef methods[] = {
     METHOD("local_decode_attn", decode<LOCAL>),
     METHOD("kv_commit", commit),
     METHOD("kv_extend", extend),
+    METHOD("kv_start", start),
     METHOD("kv_compact", compact),
     METHOD("rope_apply", rope<false>),
     METHOD("rope_apply_at", rope<true>),
+    METHOD("rope_block", block),
     METHOD("span_masked_prefill_attn", prefill<false>),
     METHOD("span_masked_prefill_attn_planned", prefill<true>),
     METHOD("span_masked_prefill_attn_cached", cached<false>),

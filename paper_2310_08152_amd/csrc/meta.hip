@@ -78,13 +78,12 @@ constexpr int ROPE_HPT = 2;
 // sequence whose rows would leave [0, y_rows) (row0 < 0 included) is not
 // written and sets SCKV_STATUS_CAP.
 template <typename T, int D>
-__global__ __launch_bounds__(256) void rope_kernel(const T* x, T* y,
-                                                   int32_t b, int32_t H, int32_t n, int64_t xs,
-                                                   int64_t ys, const int32_t* __restrict__ pos,
-                                                   int32_t L_meta, int32_t tok0, InvFreq inv,
-                                                   int rotate, int32_t hpt,
-                                                   const int32_t* __restrict__ row0,
-                                                   int32_t y_rows, int32_t* status) {
+__device__ __forceinline__ void rope_body(const T* x, T* y, int32_t b, int32_t H, int32_t n,
+                                          int64_t xs, int64_t ys,
+                                          const int32_t* __restrict__ pos, int32_t L_meta,
+                                          int32_t tok0, const InvFreq& inv, int rotate,
+                                          int32_t hpt, const int32_t* __restrict__ row0,
+                                          int32_t y_rows, int32_t* status) {
   constexpr int E = Piece<T>::E;
   constexpr int HALF = D / 2;
   constexpr int PPH = HALF / E;  // pieces per half row
@@ -146,6 +145,65 @@ __global__ __launch_bounds__(256) void rope_kernel(const T* x, T* y,
       }
       st16(dst + h * ys, a);
       st16(dst + h * ys + HALF, c);
+    }
+  }
+}
+
+template <typename T, int D>
+__global__ __launch_bounds__(256) void rope_kernel(const T* x, T* y,
+                                                   int32_t b, int32_t H, int32_t n, int64_t xs,
+                                                   int64_t ys, const int32_t* __restrict__ pos,
+                                                   int32_t L_meta, int32_t tok0, InvFreq inv,
+                                                   int rotate, int32_t hpt,
+                                                   const int32_t* __restrict__ row0,
+                                                   int32_t y_rows, int32_t* status) {
+  rope_body<T, D>(x, y, b, H, n, xs, ys, pos, L_meta, tok0, inv, rotate, hpt, row0, y_rows, status);
+}
+
+// One layer's block of a long prompt in one launch: grid.z picks the keys
+// (rotated, into the cache), the values (copied, into the cache) or the
+// queries (rotated).  A block's rows are few (4 sequences of 512 tokens, 32
+// heads of 80: 10.5 MB a tensor) and three launches spent 9.5 us each, most
+// of it starting and draining.
+template <typename T>
+struct RopeBlock {
+  const T* x[3];
+  T* y[3];
+  int64_t xs[3], ys[3];
+};
+template <typename T, int D>
+__global__ __launch_bounds__(256) void rope_block_kernel(RopeBlock<T> rb, int32_t b, int32_t H,
+                                                         int32_t n, const int32_t* __restrict__ pos,
+                                                         int32_t L_meta, int32_t tok0, InvFreq inv,
+                                                         int rotate, int32_t hpt,
+                                                         const int32_t* __restrict__ row0,
+                                                         int32_t L_cap, int32_t* status) {
+  const int z = blockIdx.z;
+  rope_body<T, D>(z == 0 ? rb.x[0] : z == 1 ? rb.x[1] : rb.x[2],
+                  z == 0 ? rb.y[0] : z == 1 ? rb.y[1] : rb.y[2], b, H, n,
+                  z == 0 ? rb.xs[0] : z == 1 ? rb.xs[1] : rb.xs[2],
+                  z == 0 ? rb.ys[0] : z == 1 ? rb.ys[1] : rb.ys[2], pos, L_meta, tok0, inv,
+                  z == 1 ? 0 : rotate, hpt, z == 2 ? nullptr : row0, L_cap, status);
+}
+
+// ---------------------------------------------------------------------------
+// bookkeeping of a whole prompt's rows: one thread per row
+// ---------------------------------------------------------------------------
+__global__ __launch_bounds__(256) void start_kernel(int32_t* __restrict__ kv_len,
+                                                    int32_t* __restrict__ tok_idx,
+                                                    int32_t* __restrict__ pos_ids,
+                                                    int32_t* __restrict__ cur_tok,
+                                                    const int32_t* __restrict__ pos,
+                                                    int32_t L_meta, int32_t n, int32_t b,
+                                                    int32_t L_cap) {
+  const int i = blockIdx.x * 256 + threadIdx.x;
+  if (i >= n) return;
+  for (int s = blockIdx.y; s < b; s += gridDim.y) {
+    tok_idx[(int64_t)s * L_cap + i] = i;
+    pos_ids[(int64_t)s * L_cap + i] = pos[(int64_t)s * L_meta + i];
+    if (i == 0) {
+      kv_len[s] = n;
+      cur_tok[s] = n;
     }
   }
 }
@@ -268,19 +326,37 @@ static int launch_rope(const void* x, void* y, int32_t b, int32_t H, int32_t n, 
   return hip_check(hipGetLastError(), "rope_apply: launch");
 }
 
-static int rope_common(const char* who, const void* x, void* y, int32_t b, int32_t H, int32_t n,
-                       int64_t x_stride_bh, int64_t y_stride_bh, int32_t d_head, sckv_dtype dt,
-                       const int32_t* pos, int32_t L_meta, int32_t tok0, float theta,
-                       const int32_t* row0, int32_t y_rows, int32_t* status, hipStream_t stream) {
-  const std::string w(who);
+template <typename T, int D>
+static int launch_rope_block(const RopeBlock<T>& rb, int32_t b, int32_t H, int32_t n,
+                             const int32_t* pos, int32_t L_meta, int32_t tok0, float theta,
+                             const int32_t* row0, int32_t L_cap, int32_t* status,
+                             hipStream_t stream) {
+  InvFreq inv;
+  for (int i = 0; i < 64; ++i) inv.w[i] = 0.0;
+  for (int i = 0; i < D / 2; ++i) inv.w[i] = std::pow((double)theta, -2.0 * i / D);
+  const int64_t per_seq = (int64_t)n * (D / 2 / Piece<T>::E);
+  if (per_seq > 0x7fffffffLL - 255) return fail(SCKV_EUNSUP, "rope_block: too many rows");
+  const int rotate = theta > 0.f ? 1 : 0;
+  const int hpt = rotate ? (H < ROPE_HPT ? H : ROPE_HPT) : 1;
+  const int64_t groups = (int64_t)b * ((H + hpt - 1) / hpt);
+  const dim3 grid((unsigned)((per_seq + 255) / 256), (unsigned)(groups < 65535 ? groups : 65535), 3);
+  rope_block_kernel<T, D><<<grid, 256, 0, stream>>>(rb, b, H, n, pos, L_meta, tok0, inv, rotate,
+                                                    hpt, row0, L_cap, status);
+  return hip_check(hipGetLastError(), "rope_block: launch");
+}
+
+static int rope_checks(const std::string& w, const void* x, const void* y, int32_t b, int32_t H,
+                       int32_t n, int64_t x_stride_bh, int64_t y_stride_bh, int32_t d_head,
+                       sckv_dtype dt, const int32_t* pos, int32_t L_meta, int32_t tok0,
+                       float theta, bool at, int32_t y_rows) {
   if (!x || !y) return fail(SCKV_EINVAL, w + ": null pointer");
   if (!valid_dtype(dt)) return fail(SCKV_EINVAL, w + ": unknown dtype");
   if (!supported_d(d_head)) return fail(SCKV_EUNSUP, w + ": d_head must be 64 or 80");
   if (b <= 0 || H <= 0 || n < 0) return fail(SCKV_EINVAL, w + ": bad sizes");
   if (x_stride_bh < (int64_t)n * d_head)
     return fail(SCKV_EINVAL, w + ": x slice stride smaller than n*d_head");
-  if (row0 ? (y_rows < n || y_stride_bh < (int64_t)y_rows * d_head)
-           : y_stride_bh < (int64_t)n * d_head)
+  if (at ? (y_rows < n || y_stride_bh < (int64_t)y_rows * d_head)
+         : y_stride_bh < (int64_t)n * d_head)
     return fail(SCKV_EINVAL, w + ": y slice smaller than its rows");
   if (!(theta >= 0.f) || std::isinf(theta)) return fail(SCKV_EINVAL, w + ": theta must be finite and >= 0");
   if (theta > 0.f) {
@@ -291,6 +367,16 @@ static int rope_common(const char* who, const void* x, void* y, int32_t b, int32
   if (!aligned16(x) || !aligned16(y) || (x_stride_bh * elem_bytes(dt)) % 16 ||
       (y_stride_bh * elem_bytes(dt)) % 16)
     return fail(SCKV_EINVAL, w + ": buffers and strides must be 16-byte aligned");
+  return SCKV_OK;
+}
+
+static int rope_common(const char* who, const void* x, void* y, int32_t b, int32_t H, int32_t n,
+                       int64_t x_stride_bh, int64_t y_stride_bh, int32_t d_head, sckv_dtype dt,
+                       const int32_t* pos, int32_t L_meta, int32_t tok0, float theta,
+                       const int32_t* row0, int32_t y_rows, int32_t* status, hipStream_t stream) {
+  const int rc = rope_checks(who, x, y, b, H, n, x_stride_bh, y_stride_bh, d_head, dt, pos, L_meta,
+                             tok0, theta, row0 != nullptr, y_rows);
+  if (rc) return rc;
   if (n == 0) return SCKV_OK;
   if (dt == SCKV_BF16)
     return d_head == 64 ? launch_rope<uint16_t, 64>(x, y, b, H, n, x_stride_bh, y_stride_bh, pos, L_meta, tok0, theta, row0, y_rows, status, stream)
@@ -317,6 +403,57 @@ extern "C" int rope_apply_at(const void* x, void* y, const int32_t* row0, int32_
   if (!row0) return fail(SCKV_EINVAL, "rope_apply_at: null row0");
   return rope_common("rope_apply_at", x, y, b, H, n, x_stride_bh, y_stride_bh, d_head, dt, pos,
                      L_meta, tok0, theta, row0, y_rows, status, stream);
+}
+
+template <typename T>
+static int rope_block_typed(const void* q, const void* k, const void* v, void* qr, void* k_cache,
+                            void* v_cache, const int32_t* row0, int32_t L_cap, int32_t b,
+                            int32_t H, int32_t n, int64_t q_s, int64_t k_s, int64_t v_s,
+                            int64_t qr_s, int64_t cache_s, int32_t d_head, const int32_t* pos,
+                            int32_t L_meta, int32_t tok0, float theta, int32_t* status,
+                            hipStream_t stream) {
+  const RopeBlock<T> rb = {{static_cast<const T*>(k), static_cast<const T*>(v), static_cast<const T*>(q)},
+                           {static_cast<T*>(k_cache), static_cast<T*>(v_cache), static_cast<T*>(qr)},
+                           {k_s, v_s, q_s},
+                           {cache_s, cache_s, qr_s}};
+  return d_head == 64 ? launch_rope_block<T, 64>(rb, b, H, n, pos, L_meta, tok0, theta, row0, L_cap, status, stream)
+                      : launch_rope_block<T, 80>(rb, b, H, n, pos, L_meta, tok0, theta, row0, L_cap, status, stream);
+}
+
+extern "C" int rope_block(const void* q, const void* k, const void* v, void* qr, void* k_cache,
+                          void* v_cache, const int32_t* row0, int32_t L_cap, int32_t b, int32_t H,
+                          int32_t n, int64_t q_stride_bh, int64_t k_stride_bh, int64_t v_stride_bh,
+                          int64_t qr_stride_bh, int64_t cache_stride_bh, int32_t d_head,
+                          sckv_dtype dt, const int32_t* pos, int32_t L_meta, int32_t tok0,
+                          float theta, int32_t* status, hipStream_t stream) {
+  clear_error();
+  if (!row0) return fail(SCKV_EINVAL, "rope_block: null row0");
+  int rc = rope_checks("rope_block", k, k_cache, b, H, n, k_stride_bh, cache_stride_bh, d_head, dt,
+                       pos, L_meta, tok0, theta, true, L_cap);
+  if (!rc)
+    rc = rope_checks("rope_block", v, v_cache, b, H, n, v_stride_bh, cache_stride_bh, d_head, dt,
+                     pos, L_meta, tok0, 0.f, true, L_cap);
+  if (!rc)
+    rc = rope_checks("rope_block", q, qr, b, H, n, q_stride_bh, qr_stride_bh, d_head, dt, pos,
+                     L_meta, tok0, theta, false, 0);
+  if (rc) return rc;
+  if (n == 0) return SCKV_OK;
+  return dt == SCKV_BF16
+             ? rope_block_typed<uint16_t>(q, k, v, qr, k_cache, v_cache, row0, L_cap, b, H, n, q_stride_bh, k_stride_bh, v_stride_bh, qr_stride_bh, cache_stride_bh, d_head, pos, L_meta, tok0, theta, status, stream)
+             : rope_block_typed<float>(q, k, v, qr, k_cache, v_cache, row0, L_cap, b, H, n, q_stride_bh, k_stride_bh, v_stride_bh, qr_stride_bh, cache_stride_bh, d_head, pos, L_meta, tok0, theta, status, stream);
+}
+
+extern "C" int kv_start(int32_t* kv_len, int32_t* tok_idx, int32_t* pos_ids, int32_t* cur_tok,
+                        const int32_t* pos, int32_t L_meta, int32_t n, int32_t b, int32_t L_cap,
+                        hipStream_t stream) {
+  clear_error();
+  if (!kv_len || !tok_idx || !pos_ids || !cur_tok || !pos)
+    return fail(SCKV_EINVAL, "kv_start: null pointer");
+  if (b <= 0 || L_cap <= 0 || L_meta <= 0 || n <= 0) return fail(SCKV_EINVAL, "kv_start: bad sizes");
+  if (n > L_cap || n > L_meta) return fail(SCKV_EINVAL, "kv_start: n exceeds L_cap or L_meta");
+  const dim3 grid((unsigned)((n + (int64_t)255) / 256), (unsigned)(b < 65535 ? b : 65535));
+  start_kernel<<<grid, 256, 0, stream>>>(kv_len, tok_idx, pos_ids, cur_tok, pos, L_meta, n, b, L_cap);
+  return hip_check(hipGetLastError(), "kv_start: launch");
 }
 
 extern "C" int kv_extend(int32_t* kv_len, int32_t* tok_idx, int32_t* pos_ids, int32_t* row0_out,

@@ -64,6 +64,11 @@ class KVCache:
 
     def start_prompt(self, L: int, meta: SpanMeta):
         """Rows [0, L) hold prompt tokens 0..L-1; the next token is L."""
+        if meta.pos.shape[0] == self.b and 0 < L <= min(self.L_cap, meta.pos.shape[1]):
+            B.kv_start(self.kv_len, self.tok_idx, self.pos_ids, self.cur_tok, meta.pos,
+                       meta.pos.shape[1], L, self.b, self.L_cap)
+            return
+        # an empty prompt, one batch's positions for all, or sizes torch refuses
         self.tok_idx[:, :L] = torch.arange(L, dtype=torch.int32, device=self.kv.device)
         self.pos_ids[:, :L] = meta.pos[:, :L]
         self.kv_len.fill_(L)
@@ -187,14 +192,11 @@ def prefill_progressive(q, k, v, o, cache: KVCache, meta: SpanMeta, ws: Workspac
         cache.extend(meta, B0, n, row0, stream=stream)
         prefill_block_plan(cache, meta, ws, B0, n, row0, stream=stream)
         for m in range(M):
-            for kv, src, th in ((0, k, theta), (1, v, 0.0)):
-                x = src[m, :, :, B0:B0 + n]
-                dst = cache.kv[m, kv]
-                B.rope_apply_at(x, dst, row0, cache.L_cap, b, H, n, x.stride(1), dst.stride(1), d,
-                                meta.pos, meta.L_meta, B0, th, status=cache.status,
-                                stream=stream)
-            B.rope_apply(q[m, :, :, B0:B0 + n], qr, b, H, n, q.stride(2), qr.stride(1), d,
-                         meta.pos, meta.L_meta, B0, theta, stream=stream)
+            qb, kb, vb = (x[m, :, :, B0:B0 + n] for x in (q, k, v))
+            dst = cache.k(m)
+            B.rope_block(qb, kb, vb, qr, dst, cache.v(m), row0, cache.L_cap, b, H, n,
+                         qb.stride(1), kb.stride(1), vb.stride(1), qr.stride(1), dst.stride(1), d,
+                         meta.pos, meta.L_meta, B0, theta, status=cache.status, stream=stream)
             prefill_block(qr[:, :, :n], cache, m, o[m, :, :, B0:B0 + n], meta, ws, B0, row0,
                           scale=scale, stream=stream, planned=True)
         nxt.fill_(B0 + n)

@@ -153,3 +153,59 @@ def test_prefill_wave_groups(d, H, L):
     assert np.isfinite(f64(o)).all()
     ref = O.masked_attention(Q, K, V, O.attention_mask(O.token_types(spans[0], L)))
     assert np.abs(Og - ref).max() <= TOL, np.abs(Og - ref).max()
+
+
+@pytest.mark.parametrize("dtype,d,theta,H,n", [("bf16", 80, 10000.0, 3, 37), ("bf16", 64, 0.0, 4, 300),
+                                               ("f32", 80, 10000.0, 1, 1), ("f32", 64, 10000.0, 5, 129)])
+def test_rope_block_is_its_three_calls(dtype, d, theta, H, n):
+    """One launch gives bit for bit what the three calls give, a sequence
+    without room included."""
+    print(f"rope_block {dtype} d={d} theta={theta} H={H} n={n}", flush=True)
+    from paper_2310_08152_amd import binding as B
+    b, L, L_cap, tok0 = 3, 400, 500, 23
+    meta = P().SpanMeta([[(3, 40)], [(30, 200), (210, 211)], []], L, DEV)
+    q, k, v = (rnd((b, H, n + 5, d), 400 + i, dtype)[:, :, 2:2 + n] for i in range(3))
+    row0 = torch.tensor([0, -1, L_cap - n], dtype=torch.int32, device=DEV)
+    got = []
+    for one in (False, True):
+        cache = torch.zeros((2, b, H, L_cap, d), dtype=q.dtype, device=DEV)
+        qr = torch.zeros((b, H, n + 1, d), dtype=q.dtype, device=DEV)
+        st = torch.zeros(1, dtype=torch.int32, device=DEV)
+        s, c = q.stride(1), cache.stride(2)
+        if one:
+            B.rope_block(q, k, v, qr, cache[0], cache[1], row0, L_cap, b, H, n, s, s, s,
+                         qr.stride(1), c, d, meta.pos, L, tok0, theta, status=st)
+        else:
+            for x, y, th in ((k, cache[0], theta), (v, cache[1], 0.0)):
+                B.rope_apply_at(x, y, row0, L_cap, b, H, n, s, c, d, meta.pos, L, tok0, th,
+                                status=st)
+            B.rope_apply(q, qr, b, H, n, s, qr.stride(1), d, meta.pos, L, tok0, theta)
+        torch.cuda.synchronize()
+        assert int(st) == B.STATUS_CAP
+        got.append((cache, qr))
+    assert torch.equal(got[0][0], got[1][0]) and torch.equal(got[0][1], got[1][1])
+    assert not got[0][0][:, 1].any() and got[0][0][0, 2, :, L_cap - n:].any()
+
+
+@pytest.mark.parametrize("L", [1, 256, 257, 300])
+def test_start_prompt_bookkeeping(L):
+    """Rows past the prompt keep what they held; a prompt longer than the
+    cache or the metadata is refused; an empty one is accepted."""
+    print(f"start_prompt L={L}", flush=True)
+    b, cap = 3, 300
+    meta = P().SpanMeta([[(0, 9)], [], [(20, 290)]], 320, DEV)
+    cache = P().KVCache(1, b, 1, cap, 64, torch.bfloat16, DEV)
+    cache.tok_idx.fill_(-7)
+    cache.pos_ids.fill_(-7)
+    cache.start_prompt(L, meta)
+    t = torch.arange(cap, dtype=torch.int32)
+    rows = (t < L).expand(b, cap)
+    assert torch.equal(cache.tok_idx.cpu(), torch.where(rows, t, -7))
+    assert torch.equal(cache.pos_ids.cpu(), torch.where(rows, meta.pos.cpu()[:, :cap], -7))
+    assert cache.kv_len.tolist() == cache.cur_tok.tolist() == [L] * b
+    with pytest.raises(RuntimeError):
+        cache.start_prompt(cap + 1, meta)
+    with pytest.raises(RuntimeError):
+        cache.start_prompt(300, P().SpanMeta([[]] * b, 200, DEV))
+    cache.start_prompt(0, meta)
+    assert cache.kv_len.tolist() == [0] * b
