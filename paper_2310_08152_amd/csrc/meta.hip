@@ -137,8 +137,10 @@ __device__ __forceinline__ void rope_body(const T* x, T* y, int32_t b, int32_t H
 #pragma unroll
         for (int e = 0; e < E; ++e) {
           const float x1 = fa[e], x2 = fc[e];
-          fa[e] = x1 * cs[e] - x2 * sn[e];
-          fc[e] = x2 * cs[e] + x1 * sn[e];
+          // the fused forms are written out: which product of a pair stays
+          // unrounded is then the same in every kernel
+          fa[e] = fmaf(x1, cs[e], -(x2 * sn[e]));
+          fc[e] = fmaf(x2, cs[e], x1 * sn[e]);
         }
         a = Piece<T>::pack(fa);
         c = Piece<T>::pack(fc);
