@@ -260,8 +260,7 @@ struct TileInfo {
 // the pair's two values, one in each result)
 __device__ __forceinline__ float max_across_halves(float x) {
   const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);
-  const float a = __uint_as_float(r[0]), b = __uint_as_float(r[1]);
-  return a > b ? a : b;
+  return __builtin_fmaxf(__uint_as_float(r[0]), __uint_as_float(r[1]));
 }
 
 constexpr int PF_ER = 4;  // ring of list entries: tile kt+2 is fetched while kt is computed
@@ -325,7 +324,9 @@ __device__ __forceinline__ void prefill_attn_body(
   __shared__ __align__(1024) char kbuf1_s[NS != 1 ? 1 : C::NBUF == 2 ? TL::KBYTES : 1024];
   __shared__ __align__(1024) char vbuf1_s[NS != 1 ? 1 : C::NBUF == 2 ? TL::VBYTES : 1024];
   __shared__ __align__(1024) char tiles[NS == 1 ? 1 : NS * 2 * TILEB];
-  __shared__ uint32_t ent_rings[NS][PF_ER][PF_BK];
+  // per entry its token and, in the second row, how many tokens after it still
+  // see it: row i sees it iff i - token, taken as unsigned, is at most that
+  __shared__ int32_t ent_rings[NS][PF_ER][2][PF_BK];
   __shared__ int32_t row_rings[NS][PF_ER][PF_BK];  // bare row index per entry
   __shared__ TileInfo info_rings[NS][PF_ER];
 
@@ -431,7 +432,9 @@ __device__ __forceinline__ void prefill_attn_body(
   for (int db = 0; db < NDB; ++db)
 #pragma unroll
     for (int i = 0; i < 16; ++i) oacc[db][i] = 0.f;
-  float m_run = -INFINITY, l_run = 0.f;
+  // the running maximum as the steps use it: negated (0 while there is none),
+  // and the value from which a step moves it
+  float m_neg = 0.f, m_next = -INFINITY, l_run = 0.f;
   f32x4 lacc = {0.f, 0.f, 0.f, 0.f};
 
   // ---- staging: list entries run two tiles ahead through an LDS ring; the
@@ -469,10 +472,13 @@ __device__ __forceinline__ void prefill_attn_body(
     if (wave == 0) {
       const int vr_n = __builtin_amdgcn_readfirstlane(sreg.vr_n);
       const int nvalid = NS == 1 ? vr_n >> 8 : min(vr_n >> 8, nvalid_of(kt));
-      ent_ring[slot][lane] = ereg;
+      const int tok = (int)(ereg & 0x00ffffffu);
+      ent_ring[slot][0][lane] = tok;
+      // ranks of 255 stand for any larger one; the block's rows end before
+      ent_ring[slot][1][lane] = in ? max(I + (int)(ereg >> 24) - tok, 0) : 0;
       // a padding row of the tile repeats the last valid row (its score is
       // masked, so any finite row will do)
-      const int row = CACHED ? rreg : (int)(ereg & 0x00ffffffu);
+      const int row = CACHED ? rreg : tok;
       row_ring[slot][lane] = lane < nvalid ? row : __builtin_amdgcn_readfirstlane(sreg.pad_row);
       if (lane == 0) {
         TileInfo ti;
@@ -515,6 +521,16 @@ __device__ __forceinline__ void prefill_attn_body(
   }
 #pragma unroll
   for (int rnd = 0; rnd < VRND; ++rnd) {
+    if constexpr (C::VSWZ) {
+      // a round moves a whole number of rows, by a multiple of 4: the later
+      // rounds' rows and pieces follow from the first's (registers saved)
+      static_assert(PF_THREADS % TL::VSLOT == 0 && PF_THREADS / TL::VSLOT % 4 == 0, "whole rows a round");
+      if (rnd > 0) {
+        v_row[rnd] = v_row[0] + rnd * (PF_THREADS / TL::VSLOT);
+        v_off[rnd] = v_off[0];
+        continue;
+      }
+    }
     const int sl = (rnd * PF_WAVES + wave) * 64 + lane;
     const int sg = sl % TL::VSLOT;
     v_row[rnd] = min(sl / TL::VSLOT, PF_BK - 1);
@@ -590,6 +606,13 @@ __device__ __forceinline__ void prefill_attn_body(
   // summary of the tile being computed, read from the ring one step early
   // so that the step starts with its key reads
   TileInfo tcur;
+  // The loop is bound by vector issue and by the matrix instructions' share of
+  // it (SQ counters at d = 64: vector instructions active 70% of the CU-busy
+  // clocks, matrix cores busy 50%), so instructions count: the running maximum
+  // is kept in the form its users take, and an element mask is one unsigned
+  // compare of a difference (3 vector instructions an element instead of 4
+  // and a scalar one).  2-4% of a layer at either head size (16 x 4096 tokens,
+  // d = 80: 1011 -> 988 us; 8 x 2048, d = 64: 120.4 -> 117.5), bit for bit.
   // A 64-key tile is weighed in softmax steps of NB 32-key blocks: scores
   // of the step, its online softmax, its share of the value product.  At
   // D = 64 a step is one block (32 keys), so only half a tile's scores and
@@ -599,7 +622,7 @@ __device__ __forceinline__ void prefill_attn_body(
   constexpr int NB = C::NB;
   auto compute = [&](int kt, const char* kcur, const char* vcur) {
     const TileInfo ti = tcur;
-    const uint32_t* tent = ent_ring[kt % PF_ER];
+    const int32_t* tent = ent_ring[kt % PF_ER][0];
     if (wave_live && ti.jmin <= Iw + 31) {
       const bool full = ti.nvalid == PF_BK && ti.jmax <= Iw && ti.vrmin >= Iw + 31 - I;
       // With one 32-key block per step, the second block is skipped where
@@ -608,8 +631,10 @@ __device__ __forceinline__ void prefill_attn_body(
       // wave's last row.
       bool skip2 = false;
       if constexpr (NB == 1) {
-        const int j32 = __builtin_amdgcn_readfirstlane((int)(tent[32] & 0x00ffffffu));
-        skip2 = ti.nvalid <= 32 || j32 > Iw + 31;
+        if (!full) {
+          const int j32 = __builtin_amdgcn_readfirstlane(tent[32]);
+          skip2 = ti.nvalid <= 32 || j32 > Iw + 31;
+        }
       }
 #pragma unroll
       for (int st = 0; st < 2 / NB; ++st) {
@@ -638,16 +663,17 @@ __device__ __forceinline__ void prefill_attn_body(
         }
         // ---- element mask on tiles not entirely visible to this wave ----
         if (!full) {
-          const int ir = qtok - I;
+          // the lane's token and key offset are worked out here again: held
+          // across the tile loop they cost registers that it needs
+          int lane_m = threadIdx.x & 63;
+          asm volatile("" : "+v"(lane_m));
+          const int tok_m = Iw + (lane_m & 31), g_m = lane_m >> 5;
 #pragma unroll
           for (int kb = 0; kb < NB; ++kb)
 #pragma unroll
             for (int vv = 0; vv < 16; ++vv) {
-              const int key = (st * NB + kb) * 32 + 8 * (vv >> 2) + 4 * g + (vv & 3);
-              const uint32_t e = tent[key];
-              const int j = (int)(e & 0x00ffffffu);
-              const int vr = (int)(e >> 24);
-              const bool vis = (j <= qtok) & (ir <= vr);
+              const int key = (st * NB + kb) * 32 + 8 * (vv >> 2) + 4 * g_m + (vv & 3);
+              const bool vis = (uint32_t)(tok_m - tent[key]) <= (uint32_t)tent[PF_BK + key];
               sacc[kb][vv] = vis ? sacc[kb][vv] : -INFINITY;
             }
         }
@@ -658,10 +684,14 @@ __device__ __forceinline__ void prefill_attn_body(
 #pragma unroll
           for (int vv = 0; vv < 16; ++vv) mx = fmaxf(mx, sacc[kb][vv]);
         mx = max_across_halves(mx) * c2;
-        const bool grow = mx > m_run + PF_RESCALE;
+        const bool grow = mx > m_next;
         if (__ballot(grow) != 0) {
-          const float alpha = grow ? fast_exp2(m_run - mx) : 1.f;  // m_run == -inf gives 0
-          if (grow) m_run = mx;
+          // without an old maximum 0
+          const float alpha = !grow ? 1.f : m_next == -INFINITY ? 0.f : fast_exp2(-m_neg - mx);
+          if (grow) {
+            m_neg = -mx;
+            m_next = mx + PF_RESCALE;
+          }
           if constexpr (MFMA_SUM) lacc *= alpha;
           else l_run *= alpha;
 #pragma unroll
@@ -669,13 +699,12 @@ __device__ __forceinline__ void prefill_attn_body(
 #pragma unroll
             for (int i = 0; i < 16; ++i) oacc[db][i] *= alpha;
         }
-        const float m_use = (m_run == -INFINITY) ? 0.f : m_run;
         float rs = 0.f;
 #pragma unroll
         for (int kb = 0; kb < NB; ++kb)
 #pragma unroll
           for (int vv = 0; vv < 16; ++vv) {
-            const float p = fast_exp2(fmaf(sacc[kb][vv], c2, -m_use));
+            const float p = fast_exp2(fmaf(sacc[kb][vv], c2, m_neg));
             sacc[kb][vv] = p;
             if constexpr (!ONES_SUM && !MFMA_SUM) rs += p;
           }
@@ -802,6 +831,7 @@ __device__ __forceinline__ void prefill_attn_body(
     auto slot = [&](int gi) {
       return reinterpret_cast<float*>(tiles) + ((gi - 1) * PF_WAVES + wave) * NR * 64 + lane;
     };
+    const float m_run = m_next == -INFINITY ? -INFINITY : -m_neg;
     if (grp > 0) {
       float* w = slot(grp);
 #pragma unroll
