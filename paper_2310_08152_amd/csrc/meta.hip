@@ -220,10 +220,10 @@ __global__ void commit_kernel(int32_t* __restrict__ kv_len, int32_t* __restrict_
   const int s = blockIdx.x * blockDim.x + threadIdx.x;
   if (s >= b) return;
   const int t = cur_tok[s];
+  const int n = kv_len[s];  // loaded along with t: a round trip less where it is used
   if (t < 0 || t >= L_meta) {
     if (status) atomicOr(status, SCKV_STATUS_TOKEN);
   } else if (vu[(int64_t)s * L_meta + t] != t) {
-    const int n = kv_len[s];
     if (n < 0 || n >= L_cap) {
       if (status) atomicOr(status, SCKV_STATUS_CAP);
     } else {

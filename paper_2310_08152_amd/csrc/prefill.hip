@@ -935,6 +935,236 @@ __global__ __launch_bounds__(PF_THREADS) void prefill_attn_kernel_f32(
                                       info, n_qt, L_pad, n_work, cc);
 }
 
+// ---------------------------------------------------------------------------
+// fp32, few workgroups: the keys split over the waves
+// ---------------------------------------------------------------------------
+// The fp32 matrix instruction takes 64 clocks for 2 of the head's elements, so
+// a wave is bound by its own products (128 of them a 64-key tile) and a short
+// prompt's few workgroups by a few CUs.  Here a workgroup has 32 query rows
+// instead of 128, and its four waves take 32 keys each of a 128-key tile; the
+// waves' partial outputs are merged through LDS.  It stages every tile four
+// times as often for the same rows, so it is for launches that leave CUs idle
+// (4 heads of 256 tokens, d = 64: 31.0 us with 128 rows a workgroup, 16.8 us so).
+template <int D, bool CACHED>
+__device__ __forceinline__ void prefill_f32_split_body(
+    const float* __restrict__ q, const float* __restrict__ k, const float* __restrict__ v,
+    float* __restrict__ o, int32_t H, int32_t L, int64_t qs, int64_t kvs, int64_t os, float c2,
+    const int32_t* __restrict__ vu, int32_t L_meta, const uint32_t* __restrict__ list,
+    const int32_t* __restrict__ count, int32_t n_pq, int32_t L_pad, int32_t n_work, PfCached cc) {
+  using C = PfCfg<float, D>;
+  using TL = PfTile<float, D>;
+  constexpr int NDB = C::DP / 32, KS = C::KSTEPS, BK = 2 * PF_BK;
+  __shared__ __align__(1024) char kbuf[2 * TL::KBYTES];
+  __shared__ __align__(1024) char vbuf[2 * TL::VBYTES];
+  __shared__ int32_t rows[BK], toks[BK], lens[BK];
+
+  int bh, qt;
+  const int n_qt = (L + 31) / 32;
+  work_item(blockIdx.x, n_work / n_qt, n_qt, &bh, &qt);
+  const int s = bh / H;
+  const int tok0 = CACHED ? cc.tok0 : 0;
+  const int64_t pblk = (int64_t)s * n_pq + qt / PF_WAVES;  // the plan's block
+  const int I = tok0 + qt / PF_WAVES * PF_BQ;              // its first token
+  const int tid = threadIdx.x;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int lane = tid & 63;
+  const int l32 = lane & 31;
+  const int g = lane >> 5;
+  const int Iw = tok0 + qt * 32;
+  const int qrow = qt * 32 + l32;  // local query row
+  const int qtok = Iw + l32;       // its token
+
+  const float* qb = q + (int64_t)bh * qs;
+  const float* kb = k + (int64_t)bh * kvs;
+  const float* vb = v + (int64_t)bh * kvs;
+  float* const orow = o + (int64_t)bh * os + (int64_t)qrow * D;
+  const uint32_t* ents = list + pblk * L_pad;
+  const uint32_t* rws = CACHED ? cc.rows + pblk * L_pad : nullptr;
+  int own_row0 = 0;
+  if constexpr (CACHED) {
+    own_row0 = cc.row0[s];
+    if (own_row0 < 0 || (int64_t)own_row0 + L > cc.L_cap) {
+      // the block's rows are not in the cache: NaN outputs, nothing read
+      if (cc.status && tid == 0 && qt == 0 && (bh % H) == 0) atomicOr(cc.status, SCKV_STATUS_CAP);
+      if (wave == 0 && qrow < L)
+        for (int e = g; e < D; e += 2) orow[e] = NAN;
+      return;
+    }
+  }
+  const int n_vis = min(max(count[pblk], 0), L_pad);  // clamped, as in prefill_attn_body
+
+  // the padding value columns are zero once and for all
+  if constexpr (C::DP != D) {
+    float* vs = reinterpret_cast<float*>(vbuf);
+    for (int i = tid; i < BK * (C::DP - D); i += 256)
+      vs[(i / (C::DP - D)) * C::VP + D + i % (C::DP - D)] = 0.f;
+  }
+  float qreg[KS];
+#pragma unroll
+  for (int kk = 0; kk < KS; ++kk) qreg[kk] = qrow < L ? qb[(int64_t)qrow * D + 2 * kk + g] : 0.f;
+
+  f32x16 oacc[NDB];
+#pragma unroll
+  for (int db = 0; db < NDB; ++db)
+#pragma unroll
+    for (int i = 0; i < 16; ++i) oacc[db][i] = 0.f;
+  float m_run = -INFINITY, l_run = 0.f;
+
+  const int slice_bytes = (int)min((int64_t)kvs * 4, (int64_t)0x7fffffff);
+  const __amdgpu_buffer_rsrc_t krs =
+      __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(kb), 0, slice_bytes, 0x00020000);
+  const __amdgpu_buffer_rsrc_t vrs =
+      __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(vb), 0, slice_bytes, 0x00020000);
+  // entry `tid` of the tile that starts at list entry e0 (threads below BK)
+  uint32_t e = PF_NONE;
+  int r = 0;
+  auto load_entry = [&](int e0) {
+    const int at = min(e0 + tid, n_vis - 1);  // past the end the last entry again
+    if (tid < BK && at >= 0) {
+      e = ents[at];
+      r = CACHED ? (int)rws[at] : (int)(e & 0x00ffffffu);
+    }
+  };
+  load_entry(0);
+  for (int e0 = 0; e0 < n_vis; e0 += BK) {
+    if (tid < BK) {
+      const bool in = e0 + tid < n_vis;
+      const int t = (int)(e & 0x00ffffffu);
+      rows[tid] = r;  // a padding row repeats the last row; its score is masked
+      toks[tid] = in ? t : (int)PF_NONE;
+      lens[tid] = in ? max(I + (int)(e >> 24) - t, 0) : 0;
+    }
+    __syncthreads();
+    for (int blk = wave; blk < 2 * TL::KSLOT; blk += 4) {
+      const int sl = blk * 64 + lane;
+      __builtin_amdgcn_raw_ptr_buffer_load_lds(krs, (lds_ptr_t)(kbuf + blk * 1024), 16,
+                                               rows[sl / TL::KSLOT] * (D * 4) + sl % TL::KSLOT * 16,
+                                               0, 0, 0);
+    }
+    for (int blk = wave; blk < 2 * TL::VSLOT; blk += 4) {
+      const int sl = blk * 64 + lane;
+      if (sl % TL::VSLOT < TL::PPR)
+        __builtin_amdgcn_raw_ptr_buffer_load_lds(vrs, (lds_ptr_t)(vbuf + blk * 1024), 16,
+                                                 rows[sl / TL::VSLOT] * (D * 4) + sl % TL::VSLOT * 16,
+                                                 0, 0, 0);
+    }
+    load_entry(e0 + BK);
+    wait_vmem();
+    __syncthreads();
+    // the list is in token order: a wave whose first key is later than the
+    // workgroup's last row has nothing to do
+    const int key0 = 32 * wave;
+    if (toks[key0] <= Iw + 31) {
+      f32x16 sacc;
+#pragma unroll
+      for (int i = 0; i < 16; ++i) sacc[i] = 0.f;
+      const float* krow = reinterpret_cast<const float*>(kbuf) + (key0 + l32) * C::KP + g;
+#pragma unroll
+      for (int kk = 0; kk < KS; ++kk)
+        sacc = __builtin_amdgcn_mfma_f32_32x32x2f32(krow[2 * kk], qreg[kk], sacc, 0, 0, 0);
+      float mx = -INFINITY;
+#pragma unroll
+      for (int vv = 0; vv < 16; ++vv) {
+        const int key = key0 + 8 * (vv >> 2) + 4 * g + (vv & 3);
+        const bool vis = (uint32_t)(qtok - toks[key]) <= (uint32_t)lens[key];
+        sacc[vv] = vis ? sacc[vv] : -INFINITY;
+        mx = fmaxf(mx, sacc[vv]);
+      }
+      mx = max_across_halves(mx) * c2;
+      const bool grow = mx > m_run + PF_RESCALE;
+      if (__ballot(grow) != 0) {
+        const float alpha = grow ? fast_exp2(m_run - mx) : 1.f;  // m_run == -inf gives 0
+        if (grow) m_run = mx;
+        l_run *= alpha;
+#pragma unroll
+        for (int db = 0; db < NDB; ++db)
+#pragma unroll
+          for (int i = 0; i < 16; ++i) oacc[db][i] *= alpha;
+      }
+      const float m_use = (m_run == -INFINITY) ? 0.f : m_run;
+#pragma unroll
+      for (int vv = 0; vv < 16; ++vv) {
+        sacc[vv] = fast_exp2(fmaf(sacc[vv], c2, -m_use));
+        l_run += sacc[vv];
+      }
+      const float* vs = reinterpret_cast<const float*>(vbuf);
+#pragma unroll
+      for (int db = 0; db < NDB; ++db)
+#pragma unroll
+        for (int vv = 0; vv < 16; ++vv) {
+          const int key = key0 + 8 * (vv >> 2) + 4 * g + (vv & 3);
+          oacc[db] = __builtin_amdgcn_mfma_f32_32x32x2f32(vs[key * C::VP + db * 32 + l32], sacc[vv],
+                                                          oacc[db], 0, 0, 0);
+        }
+    }
+    __syncthreads();
+  }
+
+  // merge: the waves' accumulators, maxima and sums to wave 0, register by register
+  l_run += __shfl_xor(l_run, 32, 64);
+  constexpr int NR = 16 * NDB + 2;
+  static_assert(3 * NR * 256 <= (int)sizeof(kbuf), "room for the partials");
+  float* const part = reinterpret_cast<float*>(kbuf) + lane;
+  if (wave > 0) {
+    float* w = part + (wave - 1) * NR * 64;
+#pragma unroll
+    for (int db = 0; db < NDB; ++db)
+#pragma unroll
+      for (int i = 0; i < 16; ++i) w[(db * 16 + i) * 64] = oacc[db][i];
+    w[16 * NDB * 64] = m_run;
+    w[(16 * NDB + 1) * 64] = l_run;
+  }
+  __syncthreads();
+  if (wave > 0 || qrow >= L) return;
+  if (vu[(int64_t)s * L_meta + qtok] == qtok) {  // a <CL> row's output is its own value row
+    const float* vrow = vb + (int64_t)(own_row0 + qrow) * D;
+    for (int d0 = 4 * g; d0 < D; d0 += 8) st16(orow + d0, ld16(vrow + d0));
+    return;
+  }
+  float m_all = m_run;
+#pragma unroll
+  for (int w = 0; w < 3; ++w) m_all = fmaxf(m_all, part[(w * NR + 16 * NDB) * 64]);
+  // a wave without a visible key for the row has weight 0 (and zeros)
+  float f = fast_exp2(m_run - m_all);
+  l_run *= f;
+#pragma unroll
+  for (int db = 0; db < NDB; ++db)
+#pragma unroll
+    for (int i = 0; i < 16; ++i) oacc[db][i] *= f;
+#pragma unroll
+  for (int w = 0; w < 3; ++w) {
+    const float* x = part + w * NR * 64;
+    f = fast_exp2(x[16 * NDB * 64] - m_all);
+    l_run = fmaf(x[(16 * NDB + 1) * 64], f, l_run);
+#pragma unroll
+    for (int db = 0; db < NDB; ++db)
+#pragma unroll
+      for (int i = 0; i < 16; ++i) oacc[db][i] = fmaf(x[(db * 16 + i) * 64], f, oacc[db][i]);
+  }
+  const float inv = 1.f / l_run;
+#pragma unroll
+  for (int db = 0; db < NDB; ++db)
+#pragma unroll
+    for (int jj = 0; jj < 4; ++jj) {
+      const int d0 = db * 32 + 8 * jj;
+      if (d0 >= D) continue;
+      u32x4 w;
+#pragma unroll
+      for (int i = 0; i < 4; ++i) w[i] = __float_as_uint(oacc[db][4 * jj + i] * inv);
+      st16(orow + d0 + 4 * g, w);
+    }
+}
+
+template <int D, bool CACHED>
+__global__ __launch_bounds__(256) void prefill_f32_split_kernel(
+    const float* __restrict__ q, const float* __restrict__ k, const float* __restrict__ v,
+    float* __restrict__ o, int32_t H, int32_t L, int64_t qs, int64_t kvs, int64_t os, float c2,
+    const int32_t* __restrict__ vu, int32_t L_meta, const uint32_t* __restrict__ list,
+    const int32_t* __restrict__ count, int32_t n_pq, int32_t L_pad, int32_t n_work, PfCached cc) {
+  prefill_f32_split_body<D, CACHED>(q, k, v, o, H, L, qs, kvs, os, c2, vu, L_meta, list, count,
+                                    n_pq, L_pad, n_work, cc);
+}
+
 template <typename T, int D, bool CACHED>
 static int launch_prefill(const void* q, const void* k, const void* v, void* o, int32_t b,
                           int32_t H, int32_t L, int64_t qs, int64_t kvs, int64_t os, float scale,
@@ -961,6 +1191,12 @@ static int launch_prefill(const void* q, const void* k, const void* v, void* o, 
         static_cast<const T*>(q), static_cast<const T*>(k), static_cast<const T*>(v),
         static_cast<T*>(o), H, L, qs, kvs, os, scale * PF_LOG2E, vu, L_meta, list, count, info,
         n_qt, L_pad, n_work, cc);
+  } else if (n_work <= PF_ONE_PER_CU) {
+    const int n_split = b * H * ((L + 31) / 32);  // at most four times n_work
+    prefill_f32_split_kernel<D, CACHED><<<n_split, 256, 0, stream>>>(
+        static_cast<const T*>(q), static_cast<const T*>(k), static_cast<const T*>(v),
+        static_cast<T*>(o), H, L, qs, kvs, os, scale * PF_LOG2E, vu, L_meta, list, count, n_qt,
+        L_pad, n_split, cc);
   } else
     prefill_attn_kernel_f32<D, CACHED><<<n_work, PF_THREADS, 0, stream>>>(
         static_cast<const T*>(q), static_cast<const T*>(k), static_cast<const T*>(v),
