@@ -559,7 +559,8 @@ __global__ __launch_bounds__(NW * 64) void decode_mfma_kernel(
   const int tp = te < HD ? te + HD : te - HD;
   const uint16_t qx_raw = q[(int64_t)bh * D + te];
   const uint16_t qp_raw = q[(int64_t)bh * D + tp];
-  const double freq = tab.w[min(te, tp)];
+  double freq = 0.0;
+  if (rotate) freq = tab.w[min(te, tp)];
   const uint16_t kx_raw = k_new[(int64_t)bh * D + te];
   const uint16_t kp_raw = k_new[(int64_t)bh * D + tp];
   const uint16_t vx_raw = v_new[(int64_t)bh * D + te];

@@ -544,7 +544,10 @@ __device__ __forceinline__ void prefill_attn_body(
   }
   // A copy in assembly has no register results; wait_vmem and the step's
   // barrier order it.  (Through the builtin, the compiler makes every LDS read
-  // wait for every copy where it cannot tell the buffers apart.)
+  // wait for every copy where it cannot tell the buffers apart.)  The compiler
+  // sees no memory instruction here, so the five wait states between a vector
+  // instruction's write of a scalar register (the descriptor's) and its use by
+  // the copy are kept in the asm, whatever stands before it.
   typedef uint32_t rsrc_t __attribute__((ext_vector_type(4)));
   auto rsrc_words = [&](const void* base) {
     const uint64_t a = reinterpret_cast<uint64_t>(base);
@@ -559,7 +562,7 @@ __device__ __forceinline__ void prefill_attn_body(
     } else {
       const uint32_t lds = (uint32_t)__builtin_amdgcn_readfirstlane(
           (int)(uint32_t)(uintptr_t)(__attribute__((address_space(3))) char*)dst);
-      asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, 0 offen lds"
+      asm volatile("s_mov_b32 m0, %0\n\ts_nop 3\n\tbuffer_load_dwordx4 %1, %2, 0 offen lds"
                    :: "s"(lds), "v"(off), "s"(rw) : "m0", "memory");
     }
   };
@@ -1073,8 +1076,11 @@ __device__ __forceinline__ void prefill_f32_split_body(
       mx = max_across_halves(mx) * c2;
       const bool grow = mx > m_run + PF_RESCALE;
       if (__ballot(grow) != 0) {
-        const float alpha = grow ? fast_exp2(m_run - mx) : 1.f;  // m_run == -inf gives 0
-        if (grow) m_run = mx;
+        // whole maxima: rescaling, here and in the merge, is by powers of two
+        // and adds no rounding to that of one wave's sums
+        const float m_new = ceilf(mx);
+        const float alpha = grow ? fast_exp2(m_run - m_new) : 1.f;  // m_run == -inf gives 0
+        if (grow) m_run = m_new;
         l_run *= alpha;
 #pragma unroll
         for (int db = 0; db < NDB; ++db)
