@@ -703,9 +703,9 @@ def measure(args, w):
     pf_ref_bytes = 4 * b * H * L * d * (2 if w.dtype == "bf16" else 4)  # Q, K, V in, O out
     ms_per_step = float(np.mean(step_ms))
 
-    # the library's launch shape: one workgroup per (sequence, head) slice from
-    # 512 slices on, chunks plus a merge kernel below
-    if b * H >= 512:
+    # the library's launch shape: one workgroup per (sequence, head) slice, or
+    # chunks plus a merge kernel where there are few slices of a long cache
+    if b * H >= 512 or (w.dtype == "bf16" and (b * H >= 192 or L_cap <= 512 + 8 * b * H)):
         dec_kernel = "decode_mfma_kernel"
         dec_launch = "one compacted_decode_attn call = one kernel, one workgroup per (sequence, head)"
     else:

@@ -323,7 +323,7 @@ int kv_compact(void* kv, void* kv_out, int32_t M, int32_t b, int32_t H, int32_t 
  *          partials of d_head + 2 floats is as much as is used beyond the
  *          required size.
  * status : nullable int32, status bits OR-ed in.
- * Launch shape: bf16 with b*H >= 256 slices, or with fewer over caches of
+ * Launch shape: bf16 with b*H >= 192 slices, or with fewer over caches of
  * at most 512 + 8 * b*H rows, and fp32 with b*H >= 512: one workgroup per
  * (sequence, head) covers all its rows and writes o (the workspace is not
  * touched).  Otherwise the rows are cut into balanced chunks of at most about

@@ -38,7 +38,12 @@ namespace sckv {
 //  * Otherwise one workgroup per slice writes the output itself (no second
 //    launch).  256 slices of 1000 / 3000 rows (d = 64) took 18.2 / 42.8 us
 //    split and 13.7 / 37.8 us so, 480 slices of 300 (d = 64) / 3000 rows
-//    (d = 80) 15.4 / 92.1 and 10.9 / 86.2 us.  Below 256 slices it depends on
+//    (d = 80) 15.4 / 92.1 and 10.9 / 86.2 us.  From DEC_ONE_MIN slices on, which
+//    fill three quarters of the CUs, eight waves a slice beat the split at any
+//    length (192 slices, d = 80: 1600 / 6000 / 12000 rows 23.9 / 70.8 / 130.5
+//    us split, 18.4 / 65.4 / 127.1 so; d = 64: 21.8 / 59.3 / 104.7 and 17.2 /
+//    59.9 / 104.9; 240 slices of 2400 rows 38.0 and 34.3, 28.8 and 24.9; but 160
+//    slices of 6000 rows, d = 64, 49.1 split, 54.1 so).  Below it depends on
 //    the rows (128 slices, d = 80: 1000 rows 16.5 split, 14.7 so; 2000 rows
 //    23.0 and 24.7; 32 slices: 300 rows 8.5 and 6.6, 1000 rows 9.6 and 11.3),
 //    of which the host knows the cache's capacity: at most
@@ -57,7 +62,7 @@ namespace sckv {
 constexpr int DEC_CH = 1024;
 constexpr int DEC_CH_MIN = 128;
 constexpr int DEC_FILL = 512;
-constexpr int DEC_ONE_MIN = 256;
+constexpr int DEC_ONE_MIN = 192;
 constexpr int DEC_ONE_ROWS = 512;
 constexpr int DEC_ONE_ROWS_PER_SLICE = 8;
 constexpr int DEC_EIGHT_ROWS = 2048;

@@ -61,12 +61,13 @@ def test_prefill_covers_every_slice(b, H):
 
 
 # (b, H, L_cap): split launches whose chunks are cut finer than 1024 rows (8,
-# 32, 96 slices), one workgroup per slice below 256 slices (a short cache) and
-# from there on, with eight waves (a cache above 2048 rows) and with four
+# 32, 96, 188 slices), one workgroup per slice below 192 slices (a short cache)
+# and from there on, with eight waves (a cache above 2048 rows) and with four
 @pytest.mark.parametrize("finer", [True, False], ids=["room", "least"])
 @pytest.mark.parametrize("d,theta", [(64, 0.0), (80, 10000.0)])
 @pytest.mark.parametrize("b,H,L_cap", [(4, 2, 2400), (4, 8, 1400), (4, 24, 1500), (4, 16, 1000),
-                                       (4, 64, 2100), (4, 64, 1100), (4, 72, 1100)])
+                                       (4, 47, 2100), (4, 48, 2100), (4, 64, 2100), (4, 64, 1100),
+                                       (4, 72, 1100)])
 def test_decode_launch_shapes(b, H, L_cap, d, theta, finer):
     """One decode step against the oracle, at chunk edges, with the workspace
     path.Workspace allocates and with the least one the library accepts."""
