@@ -64,11 +64,22 @@ constexpr int PF_GROUP = 8;
 // With more workgroups each waits for a whole CU: 1024 of d = 64 36.2 and 38.1
 // (two), 512 of d = 80 17.8 and 22.1 (4 sequences of 512 tokens, three).
 constexpr int PF_ONE_PER_CU = 256, PF_TWO_PER_CU = 512;
+// Few slices are long ones, whose heaviest blocks outlast the rest of the
+// launch: with at most eight, up to 512 workgroups of d = 80 take three groups
+// too (8 heads of 8192 tokens, half freed, 87.7 and 69.5; 80% freed 42.7 and
+// 39.7; 8 of 5120 53.4 and 36.3; 4 of 16384 166 and 120; but 8 of 12288 139
+// and 144, and ten heads of 6144, 80% freed, 33.4 and 34.5), up to 768 of
+// d = 64 two (8 of 9216 96.0 and 73.2; 8 of 12288 130 and 110, 80% freed 60.0
+// and 56.6; but 8 of 16384, 80% freed, 84.6 and 85.3).  Not over a cache,
+// where a launch's blocks all see as much (blocks of 512 tokens 1171 and 1286
+// a prompt).
 constexpr int PF_LONG = 1536;  // list entries from which four groups have tiles enough
-static int prefill_groups(int d, int n_work, int L_pad) {
-  if (d == 80) return n_work <= PF_ONE_PER_CU ? 3 : 1;
+constexpr int PF_FEW_SLICES = 8, PF_THREE_PER_CU = 768;
+static int prefill_groups(int d, int n_work, int L_pad, int slices, bool cached) {
+  const bool few = !cached && slices <= PF_FEW_SLICES;
+  if (d == 80) return n_work <= (few ? PF_TWO_PER_CU : PF_ONE_PER_CU) ? 3 : 1;
   if (n_work <= PF_ONE_PER_CU && L_pad >= PF_LONG) return 4;
-  return n_work <= PF_TWO_PER_CU ? 2 : 1;
+  return n_work <= (few ? PF_THREE_PER_CU : PF_TWO_PER_CU) ? 2 : 1;
 }
 constexpr uint32_t PF_NONE = 0x00ffffffu;  // list entry of a padding column
 constexpr float PF_LOG2E = 1.4426950408889634f;
@@ -1185,7 +1196,7 @@ static int launch_prefill(const void* q, const void* k, const void* v, void* o, 
   }
   const int n_work = b * H * n_qt;
   if constexpr (sizeof(T) == 2) {
-    const int groups = prefill_groups(D, n_work, L_pad);
+    const int groups = prefill_groups(D, n_work, L_pad, b * H, CACHED);
     auto kernel = prefill_attn_kernel_bf16<D, CACHED, 1>;
     if constexpr (D == 64) {
       if (groups == 2) kernel = prefill_attn_kernel_bf16<D, CACHED, 2>;

@@ -136,10 +136,12 @@ def test_span_metadata_plan_and_scan_round_sizes(L):
 
 # one workgroup's tiles shared among groups of waves (few workgroups: three
 # groups at d = 80, two or, for long lists, four at d = 64), with fewer tiles
-# than groups, as many, and a remainder; and one group (many workgroups)
+# than groups, as many, and a remainder; one group (many workgroups); and three
+# (d = 80) or two (d = 64) in more workgroups where the slices are few and long
 @pytest.mark.parametrize("d,H,L", [(80, 2, 1), (80, 2, 64), (80, 2, 130), (80, 2, 400), (80, 3, 901),
                                    (64, 2, 1), (64, 2, 65), (64, 2, 700), (64, 2, 1600),
-                                   (80, 140, 129), (64, 260, 129), (80, 48, 700), (64, 96, 700)])
+                                   (80, 140, 129), (64, 260, 129), (80, 48, 700), (64, 96, 700),
+                                   (80, 8, 4224), (64, 8, 8320)])
 def test_prefill_wave_groups(d, H, L):
     print(f"prefill d={d} H={H} L={L}", flush=True)
     rng = np.random.default_rng(L + d)
