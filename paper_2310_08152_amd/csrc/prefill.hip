@@ -634,9 +634,11 @@ __device__ __forceinline__ void prefill_attn_body(
   // a step is the whole tile (measured faster there, at three waves either
   // way).
   constexpr int NB = C::NB;
-  auto compute = [&](int kt, const char* kcur, const char* vcur) {
+  // With `peak`, the step's scores of the tile in tcur only give the running
+  // maximum of the rows that have none yet, from the list's first tile.
+  auto compute = [&](int kt, const char* kcur, const char* vcur, auto peak) {
     const TileInfo ti = tcur;
-    const int32_t* tent = ent_ring[kt % PF_ER][0];
+    const int32_t* tent = peak ? ent_rings[0][0][0] : ent_ring[kt % PF_ER][0];
     if (wave_live && ti.jmin <= Iw + 31) {
       const bool full = ti.nvalid == PF_BK && ti.jmax <= Iw && ti.vrmin >= Iw + 31 - I;
       // With one 32-key block per step, the second block is skipped where
@@ -698,6 +700,14 @@ __device__ __forceinline__ void prefill_attn_body(
 #pragma unroll
           for (int vv = 0; vv < 16; ++vv) mx = fmaxf(mx, sacc[kb][vv]);
         mx = max_across_halves(mx) * c2;
+        if constexpr (peak) {
+          if (m_next == -INFINITY && mx > -INFINITY) {
+            m_neg = -mx;
+            m_next = mx + PF_RESCALE;
+          }
+          if (__ballot(m_next == -INFINITY) == 0) break;
+          continue;
+        }
         const bool grow = mx > m_next;
         if (__ballot(grow) != 0) {
           // without an old maximum 0
@@ -779,7 +789,7 @@ __device__ __forceinline__ void prefill_attn_body(
       if (kt + 1 < nt) dma_rows(kt + 1, kn, vn);
     }
     if (kt + 2 < nt) load_entries(kt + 2, stg);
-    if (NS == 1 || kt < nt) compute(kt, kc, vc);
+    if (NS == 1 || kt < nt) compute(kt, kc, vc, std::false_type{});
     if (kt + 1 < nt) tcur = info_ring[(kt + 1) % PF_ER];
     if constexpr (C::NBUF == 1) {
       __syncthreads();
@@ -822,6 +832,20 @@ __device__ __forceinline__ void prefill_attn_body(
 
   wait_vmem();
   __syncthreads();
+  // The other groups start from the running maximum that the first group (and
+  // a launch of one group) takes from the list's first tile: probabilities are
+  // rounded to bf16 relative to the running maximum, and with one of its own
+  // each group rounded them otherwise than a launch of one group (outputs
+  // 1.2e-3 apart, as far as either is from 64 bits; 1e-5 so).  It costs them
+  // that tile's scores (d = 80: 777 tokens 16.2 -> 16.5 us, 300 tokens 9.3 ->
+  // 9.6; d = 64: 777 tokens 15.2 either way).  The first group's tile stays
+  // until the barrier that ends the first step.
+  if constexpr (NS > 1) {
+    if (grp > 0 && nt > 0) {
+      tcur = info_rings[0][0];
+      compute(0, tiles, nullptr, std::true_type{});
+    }
+  }
   tcur = info_ring[0];
 
   // every group takes as many steps as the first, which has the most tiles
