@@ -509,12 +509,14 @@ __device__ __forceinline__ void prefill_attn_body(
   constexpr int KRND = (TL::KSLOT + PF_WAVES - 1) / PF_WAVES;
   constexpr int VRND = (TL::VSLOT + PF_WAVES - 1) / PF_WAVES;
   // Copies go through buffer loads with an LDS destination: a 32-bit byte
-  // offset per lane against a descriptor of the slice (reads past the slice
-  // return zeros instead of faulting), the LDS block address in scalar
-  // registers.  Each lane's tile row and piece offset per round are fixed
+  // offset per lane against a descriptor of the slice's rows (at most 32768),
+  // the LDS block address in scalar registers.  The descriptor ends with the
+  // last row, not with the stride to the next slice: behind the last slice's
+  // rows the buffer may end, and what is read past the descriptor (the last
+  // row's pad slot, rows of a plan made for a longer prompt) is zero instead.  Each lane's tile row and piece offset per round are fixed
   // for the kernel and computed once here.
   const int wave_s = __builtin_amdgcn_readfirstlane(wave);
-  const int slice_bytes = (int)min((int64_t)kvs * (int64_t)sizeof(T), (int64_t)0x7fffffff);
+  const int slice_bytes = (CACHED ? cc.L_cap : L) * D * (int)sizeof(T);
   const __amdgpu_buffer_rsrc_t krs =
       __builtin_amdgcn_make_buffer_rsrc(const_cast<T*>(kb), 0, slice_bytes, 0x00020000);
   const __amdgpu_buffer_rsrc_t vrs =
@@ -526,8 +528,8 @@ __device__ __forceinline__ void prefill_attn_body(
     const int sl = (rnd * PF_WAVES + wave) * 64 + lane;
     const int sg = sl % TL::KSLOT;
     k_row[rnd] = min(sl / TL::KSLOT, PF_BK - 1);
-    // a key row's pad slot is never read, so it is copied too (whatever the
-    // 16 bytes after the row hold): no lane of a copy is masked off
+    // a key row's pad slot is never read, so it is copied too (the first 16
+    // bytes of the next row): no lane of a copy is masked off
     k_off[rnd] = sg * 16;
   }
 #pragma unroll
@@ -1048,7 +1050,7 @@ __device__ __forceinline__ void prefill_f32_split_body(
     for (int i = 0; i < 16; ++i) oacc[db][i] = 0.f;
   float m_run = -INFINITY, l_run = 0.f;
 
-  const int slice_bytes = (int)min((int64_t)kvs * 4, (int64_t)0x7fffffff);
+  const int slice_bytes = (CACHED ? cc.L_cap : L) * D * 4;  // the slice's rows, as in prefill_attn_body
   const __amdgpu_buffer_rsrc_t krs =
       __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(kb), 0, slice_bytes, 0x00020000);
   const __amdgpu_buffer_rsrc_t vrs =

@@ -183,6 +183,28 @@ def test_prefill_rounds_alike_in_every_launch(d, H, L, many):
     assert float((few.double() - all_[:, :H].double()).abs().max()) <= TOL
 
 
+# groups of waves, a single group; fp32 with 32 query rows a workgroup and 128
+@pytest.mark.parametrize("dtype,d,H", [("bf16", 80, 2), ("bf16", 64, 2), ("bf16", 80, 140),
+                                       ("bf16", 64, 270), ("f32", 80, 2), ("f32", 64, 2),
+                                       ("f32", 80, 130), ("f32", 64, 130)])
+def test_prefill_reads_only_its_rows(dtype, d, H):
+    """Rows behind the prompt's, within the stride to the next slice, are not
+    read, even where a longer prompt's plan lists them."""
+    print(f"prefill rows {dtype} d={d} H={H}", flush=True)
+    L, room = 200, 256
+    meta = P().SpanMeta([[(3, 40)]], room, DEV)
+    ws = P().Workspace(1, H, room, 1, d, DEV)
+    q = rnd((1, H, L, d), 340, dtype)
+    k, v = (torch.full((1, H, room, d), float("nan"), dtype=q.dtype, device=DEV) for _ in range(2))
+    k[:, :, :L], v[:, :, :L] = rnd((1, H, L, d), 341, dtype), rnd((1, H, L, d), 342, dtype)
+    o = [torch.full_like(q, float("nan")) for _ in range(2)]
+    for out, n in zip(o, (L, room)):
+        P().prefill_plan(meta, ws, 1, n)
+        P().prefill_layer(q, k[:, :, :L], v[:, :, :L], out, meta, ws, L, planned=True)
+    torch.cuda.synchronize()
+    assert torch.isfinite(o[0]).all() and torch.equal(o[0], o[1])
+
+
 @pytest.mark.parametrize("dtype,d,theta,H,n", [("bf16", 80, 10000.0, 3, 37), ("bf16", 64, 0.0, 4, 300),
                                                ("f32", 80, 10000.0, 1, 1), ("f32", 64, 10000.0, 5, 129)])
 def test_rope_block_is_its_three_calls(dtype, d, theta, H, n):
