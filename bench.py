@@ -705,7 +705,7 @@ def measure(args, w):
 
     # the library's launch shape: one workgroup per (sequence, head) slice, or
     # chunks plus a merge kernel where there are few slices of a long cache
-    if b * H >= 512 or (w.dtype == "bf16" and (b * H >= 192 or L_cap <= 512 + 8 * b * H)):
+    if b * H >= 512 or (w.dtype == "bf16" and L_cap <= min(512 + 8 * b * H, 1536)):
         dec_kernel = "decode_mfma_kernel"
         dec_launch = "one compacted_decode_attn call = one kernel, one workgroup per (sequence, head)"
     else:

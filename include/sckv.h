@@ -323,10 +323,9 @@ int kv_compact(void* kv, void* kv_out, int32_t M, int32_t b, int32_t H, int32_t 
  *          partials of d_head + 2 floats is as much as is used beyond the
  *          required size.
  * status : nullable int32, status bits OR-ed in.
- * Launch shape: bf16 with b*H >= 192 slices, or with fewer over caches of
- * at most 512 + 8 * b*H rows, and fp32 with b*H >= 512: one workgroup per
- * (sequence, head) covers all its rows and writes o (the workspace is not
- * touched).  Otherwise the rows are cut into balanced chunks of at most about
+ * Launch shape: with b*H >= 512 slices, and bf16 with fewer over caches of
+ * at most min(512 + 8 * b*H, 1536) rows: one workgroup per (sequence, head)
+ * covers all its rows and writes o (the workspace is not touched).  Otherwise the rows are cut into balanced chunks of at most about
  * 1024 rows, one workgroup each, and a second kernel merges the chunk
  * partials (log-sum-exp) into o.  bf16 scores are computed on the matrix cores with
  * q carried as two bf16 terms (about fp32 accuracy).

@@ -28,7 +28,7 @@
 namespace sckv {
 
 // Launch shapes, measured on MI355X.  A slice is one (sequence, head) pair.
-//  * bf16, few slices (below DEC_ONE_MIN) of a long cache: each slice is cut
+//  * bf16, fewer than DEC_SINGLE_MIN slices of a long cache: each slice is cut
 //    into chunks, one 4-wave workgroup each, and a second kernel merges the
 //    chunk partials.  A chunk has about DEC_CH rows at most; a launch of few
 //    slices is cut finer, to DEC_FILL workgroups or chunks of DEC_CH_MIN rows,
@@ -36,36 +36,35 @@ namespace sckv {
 //    d = 80: 18.2 us in chunks of DEC_CH, 9.6 us in chunks of 128; a target of
 //    1024 workgroups was up to 27% slower, one of 256 within 3%).
 //  * Otherwise one workgroup per slice writes the output itself (no second
-//    launch).  256 slices of 1000 / 3000 rows (d = 64) took 18.2 / 42.8 us
-//    split and 13.7 / 37.8 us so, 480 slices of 300 (d = 64) / 3000 rows
-//    (d = 80) 15.4 / 92.1 and 10.9 / 86.2 us.  From DEC_ONE_MIN slices on, which
-//    fill three quarters of the CUs, eight waves a slice beat the split at any
-//    length (192 slices, d = 80: 1600 / 6000 / 12000 rows 23.9 / 70.8 / 130.5
-//    us split, 18.4 / 65.4 / 127.1 so; d = 64: 21.8 / 59.3 / 104.7 and 17.2 /
-//    59.9 / 104.9; 240 slices of 2400 rows 38.0 and 34.3, 28.8 and 24.9; but 160
-//    slices of 6000 rows, d = 64, 49.1 split, 54.1 so).  Below it depends on
-//    the rows (128 slices, d = 80: 1000 rows 16.5 split, 14.7 so; 2000 rows
-//    23.0 and 24.7; 32 slices: 300 rows 8.5 and 6.6, 1000 rows 9.6 and 11.3),
-//    of which the host knows the cache's capacity: at most
-//    DEC_ONE_ROWS + DEC_ONE_ROWS_PER_SLICE * slices rows.
-//    Waves per slice: the most (8, 4, 2 or 1; 8 only for caches of more than
-//    DEC_EIGHT_ROWS rows, 1 only where d <= 64) with which every wave of the
-//    launch is resident at once (the kernel holds two waves per SIMD), so the
-//    launch runs in one round; where even one wave per slice exceeds that, 4
-//    waves, whose shorter workgroups balance the rounds best.  Measured: 256
-//    slices of 1000 rows (d = 64) 14.3 us with 4 waves, 13.7 with 8, of 500
-//    rows (d = 80) 11.4 and 12.0; 512 slices (d = 80) 4 waves; 2048 slices
-//    (d = 64) 1 wave 2% faster than 2 and 4% faster than 4; 8192 slices
-//    (d = 80) 4 waves 2.5% faster than 2.
+//    launch).  Below DEC_SINGLE_MIN slices only over short caches, because a
+//    batch's lengths differ and one long slice then outlasts the launch on its
+//    one CU.  The host knows the cache's capacity alone: the line is at
+//    DEC_ONE_ROWS + DEC_ONE_ROWS_PER_SLICE * slices rows, and at most
+//    DEC_ONE_MAX_ROWS, up to which the most unequal batch (one sequence that
+//    fills the cache, the others 500 rows) is not slower than in chunks of
+//    DEC_CH and equal lengths are faster.  us split and so, d = 64: 192 slices
+//    in a cache of 1536 rows 16.5 and 15.5 (equal lengths 22.0 and 17.2), 480
+//    slices 20.7 and 22.6 (in chunks of DEC_CH 22.6; equal 39.5 and 35.1), 160
+//    slices of 1500 10.7 and 13.9 (13.8; equal 18.2 and 16.6).  Above it the
+//    loss grows without end: 192 slices, 3072 / 16000 rows 18.9 / 44.5 and
+//    27.1 / 120 (equal 36.2 / 140 and 30.7 / 141), 384 slices of 2048 rows 22.1
+//    and 25.6 (equal 40.8 and 43.1).  Fewer slices leave CUs idle (32 slices of
+//    512 / 1000 rows, equal, d = 64: 7.7 / 7.8 split, 6.9 / 10.8 so).
+//    Waves per slice (bf16): the most (4, 2 or 1; 1 only where d <= 64) with
+//    which every wave of the launch is resident at once (the kernel holds two
+//    waves per SIMD), so the launch runs in one round; where even one wave per
+//    slice exceeds that, 4 waves, whose shorter workgroups balance the rounds
+//    best.  Measured: 512 slices (d = 80) 4 waves; 2048 slices (d = 64) 1 wave
+//    2% faster than 2 and 4% faster than 4; 8192 slices (d = 80) 4 waves 2.5%
+//    faster than 2.
 //  * fp32: split below DEC_SINGLE_MIN slices; from there on one workgroup per
 //    slice of 512 threads, of 256 from DEC_NARROW_MIN slices on.
 constexpr int DEC_CH = 1024;
 constexpr int DEC_CH_MIN = 128;
 constexpr int DEC_FILL = 512;
-constexpr int DEC_ONE_MIN = 192;
 constexpr int DEC_ONE_ROWS = 512;
 constexpr int DEC_ONE_ROWS_PER_SLICE = 8;
-constexpr int DEC_EIGHT_ROWS = 2048;
+constexpr int DEC_ONE_MAX_ROWS = 1536;
 constexpr int DEC_SINGLE_MIN = 512;
 constexpr int DEC_NARROW_MIN = 1024;
 constexpr int DEC_WAVES_PER_SIMD = 2;  // decode_mfma_kernel's occupancy (its register count)
@@ -797,6 +796,13 @@ __global__ __launch_bounds__(NW * 64) void decode_mfma_kernel(
   }
 }
 
+// whether one workgroup per slice writes the output (no partials)
+static bool one_workgroup(bool bf16, int64_t slices, int L_cap) {
+  if (slices >= DEC_SINGLE_MIN) return true;
+  return bf16 && L_cap <= std::min<int64_t>(DEC_ONE_ROWS + DEC_ONE_ROWS_PER_SLICE * slices,
+                                            DEC_ONE_MAX_ROWS);
+}
+
 static int n_chunks(int L_cap) { return (L_cap + DEC_CH - 1) / DEC_CH; }
 
 template <typename T, int D>
@@ -821,18 +827,14 @@ static int launch_decode(const void* q, const void* k_new, const void* v_new, vo
   const float qs = scale * LOG2E;
   const int slices = b * H;
   const FastDiv by_H = make_div((uint32_t)H), by_slices = make_div((uint32_t)slices);
-  const bool one = sizeof(T) == 2 ? slices >= DEC_ONE_MIN ||
-                                        L_cap <= DEC_ONE_ROWS + DEC_ONE_ROWS_PER_SLICE * slices
-                                  : slices >= DEC_SINGLE_MIN;
-  if (one) {
+  if (one_workgroup(sizeof(T) == 2, slices, L_cap)) {
     const bool narrow = slices >= DEC_NARROW_MIN;
     if constexpr (sizeof(T) == 2) {
       int cus = 0;
       const int rc = device_cus(&cus);
       if (rc) return rc;
       const int64_t slots = (int64_t)cus * 4 * DEC_WAVES_PER_SIMD;  // resident waves
-      const int nw = (int64_t)slices * 8 <= slots && L_cap > DEC_EIGHT_ROWS ? 8
-                     : (int64_t)slices * 4 <= slots   ? 4
+      const int nw = (int64_t)slices * 4 <= slots   ? 4
                      : (int64_t)slices * 2 <= slots ? 2
                      : slices <= slots              ? (D <= 64 ? 1 : 2)
                                                     : 4;
@@ -840,14 +842,13 @@ static int launch_decode(const void* q, const void* k_new, const void* v_new, vo
       // to hold long slices: both first blocks of every wave are then read
       // before the slice length arrives (rows past a shorter slice are read
       // for nothing, never used).
-      const bool spec2 = ring == 0 && nw < 8 && (int64_t)L_cap >= (int64_t)DEC_SPEC2_ROWS * nw;
+      const bool spec2 = ring == 0 && (int64_t)L_cap >= (int64_t)DEC_SPEC2_ROWS * nw;
 #define SCKV_DECODE_LAUNCH(DD, NWW, SP)                                                          \
   decode_mfma_kernel<DD, NWW, true, SP><<<slices, NWW * 64, 0, stream>>>(                         \
       qq, kn, vn, kc, vc, kv_len, cur_tok, vu, pos, L_meta, H, L_cap, qs, rotate, tab, part, 1,  \
       by_H, by_slices, slices, Split{1, 1}, out, status, ring)
       constexpr int D1 = D <= 64 ? D : 64;  // nw == 1 only where D <= 64
-      if (nw == 8) SCKV_DECODE_LAUNCH(D, 8, false);
-      else if (nw == 1 && spec2) SCKV_DECODE_LAUNCH(D1, 1, true);
+      if (nw == 1 && spec2) SCKV_DECODE_LAUNCH(D1, 1, true);
       else if (nw == 1) SCKV_DECODE_LAUNCH(D1, 1, false);
       else if (nw == 2 && spec2) SCKV_DECODE_LAUNCH(D, 2, true);
       else if (nw == 2) SCKV_DECODE_LAUNCH(D, 2, false);

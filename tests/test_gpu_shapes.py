@@ -61,8 +61,7 @@ def test_prefill_covers_every_slice(b, H):
 
 
 # (b, H, L_cap): split launches whose chunks are cut finer than 1024 rows (8,
-# 32, 96, 188 slices), one workgroup per slice below 192 slices (a short cache)
-# and from there on, with eight waves (a cache above 2048 rows) and with four
+# 32, 96, 188, 192, 256 slices) and one workgroup per slice (a short cache)
 @pytest.mark.parametrize("finer", [True, False], ids=["room", "least"])
 @pytest.mark.parametrize("d,theta", [(64, 0.0), (80, 10000.0)])
 @pytest.mark.parametrize("b,H,L_cap", [(4, 2, 2400), (4, 8, 1400), (4, 24, 1500), (4, 16, 1000),
@@ -99,6 +98,40 @@ def test_decode_launch_shapes(b, H, L_cap, d, theta, finer):
         # fp32 sums; the output's bf16 rounding, and the new key's
         assert np.abs(Og[s] - ref).max() <= TOL, (s, np.abs(Og[s] - ref).max())
         assert np.array_equal(f64(cache.kv[0, 1, s, :, lens[s]]), VN[s])
+
+
+# (slices, L_cap, one): the line between one workgroup per slice and the split
+@pytest.mark.parametrize("d", [64, 80])
+@pytest.mark.parametrize("slices,L_cap,one", [(32, 768, True), (32, 769, False), (160, 1536, True),
+                                              (192, 1537, False), (256, 3000, False),
+                                              (511, 1536, True), (511, 1537, False),
+                                              (512, 1537, True)])
+def test_decode_splits_long_slices(slices, L_cap, one, d):
+    """Below 512 slices a long cache is split, so that one long slice among
+    short ones does not stay on one CU; a launch of one workgroup per slice
+    leaves the workspace alone."""
+    print(f"decode split slices={slices} L_cap={L_cap} d={d}", flush=True)
+    b = slices if slices == 511 else 8
+    H = slices // b
+    lens = [L_cap - 1] + [40 + s % 200 for s in range(b - 1)]
+    meta = P().SpanMeta([[]] * b, L_cap + 8, DEV)
+    cache = P().KVCache(1, b, H, L_cap, d, torch.bfloat16, DEV)
+    cache.kv.copy_(rnd((1, 2, 1, 1, L_cap, d), 91).expand_as(cache.kv))
+    cache.kv_len.copy_(torch.tensor(lens, dtype=torch.int32))
+    cache.cur_tok.copy_(cache.kv_len)
+    ws = P().Workspace(b, H, 1, L_cap, d, DEV)
+    ws.decode.fill_(0x5a)
+    q, kn, vn = (rnd((b, H, d), 92 + i) for i in range(3))
+    o = torch.full_like(q, float("nan"))
+    K, V = (f64(x[:1].expand(H, -1, -1)) for x in (cache.kv[0, 0, 0], cache.kv[0, 1, 0]))
+    P().decode_layer(q, kn, vn, cache, 0, meta, ws, o)
+    torch.cuda.synchronize()
+    assert bool((ws.decode == 0x5a).all()) == one
+    Q, KN, VN, Og = f64(q), f64(kn), f64(vn), f64(o)
+    for s in sorted({0, 1, b // 2, b - 1}):
+        ref = O.decode_attention(Q[s], KN[s], VN[s], K, V, lens[s], False)
+        # fp32 sums; the output's bf16 rounding, and the new key's
+        assert np.abs(Og[s] - ref).max() <= TOL, s
 
 
 @pytest.mark.parametrize("L", [1, 1023, 1025, 4096, 4097, 9000])
