@@ -345,15 +345,18 @@ int compacted_decode_attn(const void* q, const void* k_new, const void* v_new, v
  *
  * Same arguments, semantics, precondition, status bits and outputs as
  * compacted_decode_attn, minus ws / ws_bytes: the split-K partials of a
- * launch with fewer than 512 (sequence, head) slices go to a scratch array
- * of SCKV_NOALLOC_SCRATCH_BYTES bytes inside the library, one per device,
- * held from the library's load until the process ends.  The call allocates
- * and frees nothing; its first call on a device looks up that device's
- * array address once.
- * Limit: with b*H < 512, sckv_decode_workspace_bytes(b, H, L_cap, d_head)
- * must not exceed SCKV_NOALLOC_SCRATCH_BYTES (511 slices of up to 65536
- * rows fit, at either head size); larger shapes return SCKV_EUNSUP and
- * enqueue nothing.  With b*H >= 512 the scratch array is not used.
+ * launch that is split (see there) go to a scratch array of
+ * SCKV_NOALLOC_SCRATCH_BYTES bytes inside the library, one per device, held
+ * from the library's load until the process ends.  The call allocates and
+ * frees nothing; its first call on a device looks up that device's array
+ * address once.  The outputs are bit for bit those of compacted_decode_attn
+ * with a workspace of sckv_decode_workspace_bytes(b, H, L_cap, d_head) bytes;
+ * a larger workspace may split finer, which changes the order of the fp32
+ * sums.
+ * Limit: where the launch is split, sckv_decode_workspace_bytes(b, H, L_cap,
+ * d_head) must not exceed SCKV_NOALLOC_SCRATCH_BYTES (511 slices of up to
+ * 65536 rows fit, at either head size); larger shapes return SCKV_EUNSUP and
+ * enqueue nothing.  Otherwise the scratch array is not used.
  * Every call on a device shares its array and overwrites what the previous
  * call left there (nothing in it needs clearing); calls that may overlap on
  * one device (two host threads, or two streams without ordering) race and

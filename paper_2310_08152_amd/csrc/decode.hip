@@ -1040,8 +1040,9 @@ extern "C" int compacted_decode_attn_noalloc(const void* q, const void* k_new, c
   int rc = decode_checks(W, q, k_new, v_new, k_cache, v_cache, kv_len, cur_tok, vu, pos, L_meta,
                          o, b, H, L_cap, d_head, dt, scale, rope_theta);
   if (rc) return rc;
-  // only the split launch (fewer than DEC_SINGLE_MIN slices) writes partials
-  const size_t need = (int64_t)b * H >= DEC_SINGLE_MIN
+  // only a split launch writes partials; it splits as with the least workspace,
+  // whose outputs it gives bit for bit
+  const size_t need = one_workgroup(dt == SCKV_BF16, (int64_t)b * H, L_cap)
                           ? 0 : sckv_decode_workspace_bytes(b, H, L_cap, d_head);
   if (need > SCKV_NOALLOC_SCRATCH_BYTES)
     return fail(SCKV_EUNSUP, std::string(W) + ": the split-K partials need " +

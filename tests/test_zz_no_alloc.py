@@ -99,6 +99,14 @@ def test_noalloc_decode_one_workgroup_per_slice():
     one_step(2, 256, 80, 400, [300, 399], 1e4, 31)
 
 
+@pytest.mark.parametrize("L_cap", [1400, 1700])
+def test_noalloc_decode_on_both_sides_of_the_split(L_cap):
+    """Between 192 and 511 slices: unsplit over a short cache, split over a
+    longer one."""
+    print(f"noalloc decode: b=4 H=50 d=64 L_cap={L_cap}", flush=True)
+    one_step(4, 50, 64, L_cap, [L_cap - 1, 3, 700, 1100], 0.0, 41)
+
+
 def test_noalloc_rejects_partials_beyond_the_scratch_array():
     b, H, d, L_cap = 1, 511, 80, 200000  # 511 slices x 196 chunks x 328 bytes > 16 MiB
     assert B().sckv_decode_workspace_bytes(b, H, L_cap, d) > B().NOALLOC_SCRATCH_BYTES
