@@ -64,11 +64,15 @@ class KVCache:
 
     def start_prompt(self, L: int, meta: SpanMeta):
         """Rows [0, L) hold prompt tokens 0..L-1; the next token is L."""
-        if meta.pos.shape[0] == self.b and 0 < L <= min(self.L_cap, meta.pos.shape[1]):
-            B.kv_start(self.kv_len, self.tok_idx, self.pos_ids, self.cur_tok, meta.pos,
-                       meta.pos.shape[1], L, self.b, self.L_cap)
+        pos = meta.pos
+        if (pos.is_cuda and pos.device == self.kv_len.device and pos.dtype == torch.int32
+                and pos.dim() == 2 and pos.is_contiguous() and pos.shape[0] == self.b
+                and 0 < L <= min(self.L_cap, pos.shape[1])):
+            B.kv_start(self.kv_len, self.tok_idx, self.pos_ids, self.cur_tok, pos, pos.shape[1], L,
+                       self.b, self.L_cap)
             return
-        # an empty prompt, one batch's positions for all, or sizes torch refuses
+        # an empty prompt, one sequence's positions for all, positions of another
+        # type, layout or device, a cache on the host, or sizes torch refuses
         self.tok_idx[:, :L] = torch.arange(L, dtype=torch.int32, device=self.kv.device)
         self.pos_ids[:, :L] = meta.pos[:, :L]
         self.kv_len.fill_(L)

@@ -1,6 +1,9 @@
 """Properties of the seeded input generators (harness only)."""
+from types import SimpleNamespace
+
 import numpy as np
 import pytest
+import torch
 
 from paper_2310_08152_amd import workload as W
 
@@ -62,3 +65,32 @@ def test_randn_rounds_to_bf16():
     assert x.dtype == torch.bfloat16
     y = W.randn((4, 5), seed=3, dtype="f32")
     assert torch.equal(x, y.to(torch.bfloat16))
+
+
+POSITIONS = {
+    "int32": lambda t: t,
+    "int64": lambda t: t.long(),
+    "column-major": lambda t: t.t().contiguous().t(),
+    "row-slice": lambda t: torch.cat([t, t], 1)[:, :t.shape[1]],
+    "one-for-all": lambda t: t[:1],
+}
+
+
+@pytest.mark.parametrize("form", list(POSITIONS))
+@pytest.mark.parametrize("dev", ["cpu", pytest.param("cuda", marks=pytest.mark.gpu)])
+def test_start_prompt_takes_any_positions(dev, form):
+    """Whatever torch can copy into the bookkeeping: host caches, positions of
+    another integer type, in views, or one sequence's for all."""
+    if dev == "cuda" and not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_2310_08152_amd import path as P
+    cache = P.KVCache(1, 3, 1, 10, 64, torch.float32, dev)
+    pos = POSITIONS[form](torch.arange(36, dtype=torch.int32).view(3, 12) % 7)
+    for where in {dev, "cpu"}:
+        cache.pos_ids.zero_()
+        cache.start_prompt(5, SimpleNamespace(pos=pos.to(where)))
+        want = torch.zeros(3, 10, dtype=torch.int32)
+        want[:, :5] = pos[:, :5]
+        assert torch.equal(cache.pos_ids.cpu(), want)
+        assert cache.tok_idx[:, :5].tolist() == [[0, 1, 2, 3, 4]] * 3
+        assert cache.kv_len.tolist() == cache.cur_tok.tolist() == [5] * 3
