@@ -54,14 +54,15 @@ class Args {
     if (over) throw Defer();
     return v;
   }
-  float f32() {
+  double f64() {
     PyObject* o = a_[at_++];
-    if (PyFloat_Check(o)) return (float)PyFloat_AS_DOUBLE(o);
+    if (PyFloat_Check(o)) return PyFloat_AS_DOUBLE(o);
     if (!PyLong_Check(o)) throw Defer();
     const double v = PyLong_AsDouble(o);
     if (v == -1.0 && PyErr_Occurred()) throw Defer();
-    return (float)v;
+    return v;
   }
+  float f32() { return (float)f64(); }
   // a tensor on a GPU; null for None
   const at::Tensor* tensor() {
     PyObject* o = a_[at_++];
@@ -188,7 +189,9 @@ PyObject* decode(PyObject* const* a, Py_ssize_t n) {
   const int32_t L_meta = g.i32();
   const at::Tensor* o = g.tensor();
   const int32_t b = g.i32(), H = g.i32(), L_cap = g.i32(), d = g.i32();
-  const float scale = g.f32(), theta = g.f32();
+  const float scale = g.f32();
+  const double theta_in = g.f64();  // 0 by value, not by its rounding: pos is needed otherwise
+  const float theta = (float)theta_in;
   const at::Tensor* ws = KIND == NOALLOC ? nullptr : g.tensor();
   const at::Tensor* st = g.tensor();
   if (!q) throw Defer();
@@ -197,7 +200,7 @@ PyObject* decode(PyObject* const* a, Py_ssize_t n) {
   const int64_t nh = times({b, H, d}), nc = times({b, H, L_cap, d}), nm = times({b, L_meta});
   void *pq = floats(q, nh, dt), *pkn = floats(kn, nh, dt), *pvn = floats(vn, nh, dt),
        *pkc = floats(kc, nc, dt), *pvc = floats(vc, nc, dt), *po = floats(o, nh, dt);
-  const int32_t *pvu = ints(vu, nm), *ppos = ints(pos, nm, theta == 0.f), *pcur = ints(cur, b);
+  const int32_t *pvu = ints(vu, nm), *ppos = ints(pos, nm, theta_in == 0.0), *pcur = ints(cur, b);
   int32_t* pst = word(st);
   if (KIND == LOCAL) {
     const Work w = workspace(ws);
@@ -281,12 +284,13 @@ PyObject* rope(PyObject* const* a, Py_ssize_t n) {
   const int32_t d = g.i32();
   const at::Tensor* pos = g.tensor();
   const int32_t L_meta = g.i32(), tok0 = g.i32();
-  const float theta = g.f32();
+  const double theta_in = g.f64();
+  const float theta = (float)theta_in;
   const at::Tensor* st = AT ? g.tensor() : nullptr;
   if (!x) throw Defer();
   const sckv_dtype dt = type_code(*x);
   void *px = rows(x, b, H, rows_, d, xs, dt), *py = rows(y, b, H, AT ? y_rows : rows_, d, ys, dt);
-  const int32_t* ppos = ints(pos, times({b, L_meta}), theta == 0.f);
+  const int32_t* ppos = ints(pos, times({b, L_meta}), theta_in == 0.0);
   const int32_t* prow = AT ? ints(row0, b) : nullptr;
   int32_t* pst = word(st);
   const hipStream_t stream = g.stream(x);
@@ -306,14 +310,15 @@ PyObject* block(PyObject* const* a, Py_ssize_t n) {
   const int32_t d = g.i32();
   const at::Tensor* pos = g.tensor();
   const int32_t L_meta = g.i32(), tok0 = g.i32();
-  const float theta = g.f32();
+  const double theta_in = g.f64();
+  const float theta = (float)theta_in;
   const at::Tensor* st = g.tensor();
   if (!q) throw Defer();
   const sckv_dtype dt = type_code(*q);
   void *pq = rows(q, b, H, rows_, d, qs, dt), *pk = rows(k, b, H, rows_, d, ks, dt),
        *pv = rows(v, b, H, rows_, d, vs, dt), *pr = rows(qr, b, H, rows_, d, qrs, dt),
        *pkc = rows(kc, b, H, L_cap, d, cs, dt), *pvc = rows(vc, b, H, L_cap, d, cs, dt);
-  const int32_t *ppos = ints(pos, times({b, L_meta}), theta == 0.f), *prow = ints(row0, b);
+  const int32_t *ppos = ints(pos, times({b, L_meta}), theta_in == 0.0), *prow = ints(row0, b);
   int32_t* pst = word(st);
   const hipStream_t stream = g.stream(q);
   return status_of([&] {

@@ -71,3 +71,18 @@ def test_native_and_python_checks_agree(B, form, monkeypatch):
     assert got[0][0] == got[1][0], got
     if got[0][1] is not None:
         assert torch.equal(got[0][1], got[1][1])
+
+
+@pytest.mark.gpu
+def test_native_half_keeps_positions_required(B):
+    """A rotary base that is not zero needs positions, also one that rounds to
+    zero in 32 bits."""
+    print("binding theta", flush=True)
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    x = torch.zeros(1, 1, 4, 64, device=DEV)
+    for theta in (1e-60, 1e4):
+        assert B._nat().rope_apply(x, x, 1, 1, 4, 256, 256, 64, None, 4, 0, theta, None) is None
+        with pytest.raises(B.SckvError) as e:
+            B.rope_apply(x, x, 1, 1, 4, 256, 256, 64, None, 4, 0, theta)
+        assert e.value.code == B.EINVAL
