@@ -522,6 +522,13 @@ __device__ __forceinline__ void prefill_attn_body(
   const __amdgpu_buffer_rsrc_t vrs =
       __builtin_amdgcn_make_buffer_rsrc(const_cast<T*>(vb), 0, slice_bytes, 0x00020000);
   constexpr int ROWB = D * (int)sizeof(T);
+  // Over a cache at D = 64 the registers don't suffice for all of them (the one
+  // spilled was reloaded in the middle of a step's copies, behind a wait for
+  // every copy before it): wave 0, which alone copies a key block in the last
+  // round, works that round's piece offset out from its row (5 x 32 blocks of
+  // 512 tokens over 1500 rows 50.7 -> 49.0 us, 8 x 32 over 600 29.1 -> 28.3).
+  constexpr bool LATE_K = CACHED && BF && D == 64 && NS == 1;
+  static_assert(!LATE_K || TL::KSLOT % PF_WAVES == 1, "the last round is wave 0's");
   int k_row[KRND], k_off[KRND], v_row[VRND], v_off[VRND];
 #pragma unroll
   for (int rnd = 0; rnd < KRND; ++rnd) {
@@ -589,8 +596,17 @@ __device__ __forceinline__ void prefill_attn_body(
 #pragma unroll
     for (int rnd = 0; rnd < KRND; ++rnd) {
       const int blk = rnd * PF_WAVES + wave_s;
-      if (blk < TL::KSLOT)
-        copy_rows(krs, krw, kdst + blk * 1024, kj[rnd] * ROWB + k_off[rnd]);
+      if (blk < TL::KSLOT) {
+        int off = k_off[rnd];
+        if constexpr (LATE_K) {
+          if (rnd == KRND - 1) {
+            int lane_k = lane, row_k = k_row[rnd];
+            asm volatile("" : "+v"(lane_k), "+v"(row_k));  // not ahead of the loop
+            off = (rnd * PF_THREADS + lane_k - row_k * TL::KSLOT) * 16;
+          }
+        }
+        copy_rows(krs, krw, kdst + blk * 1024, kj[rnd] * ROWB + off);
+      }
     }
 #pragma unroll
     for (int rnd = 0; rnd < VRND; ++rnd) {
