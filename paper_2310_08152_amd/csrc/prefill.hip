@@ -1000,7 +1000,25 @@ __global__ __launch_bounds__(PF_THREADS) void prefill_attn_kernel_f32(
 // instead of 128, and its four waves take 32 keys each of a 128-key tile; the
 // waves' partial outputs are merged through LDS.  It stages every tile four
 // times as often for the same rows, so it is for launches that leave CUs idle
-// (4 heads of 256 tokens, d = 64: 31.0 us with 128 rows a workgroup, 16.8 us so).
+// (4 heads of 256 tokens, d = 64: 29.5 us with 128 rows a workgroup, 16.0 us so).
+// A CU holds two such workgroups at d = 64, one at d = 80 (73 and 98 KB of LDS):
+// the line is at one round of them, at d = 80 at two where there are tiles
+// enough to split, and at more for long prompts, whose light blocks leave room
+// (over a cache all blocks see as much).  us with 128 rows a workgroup and so:
+//   d = 64: 128 heads of 128 tokens (512 workgroups) 19.6 and 18.6, 64 of 256
+//     30.2 and 20.8; 96 of 256 (768) 30.6 and 39.0; 48 of 512 (768) 46.7 and
+//     43.0, 64 of 512 (1024) 45.9 and 49.6; 32 of 1000 (1024) 72.4 and 68.6; 64
+//     of 512 over a cache of 1500 rows (1024) 136 and 143
+//   d = 80: 64 heads of 128 tokens (256 workgroups) 23.4 and 15.5, 96 of 128
+//     (384) 23.8 and 28.9; 64 of 256 (512) 37.2 and 33.9, 48 of 512 (768) 59.1
+//     and 63.5; 16 of 1500 (752) 125 and 113, 32 of 1000 (1024) 92.5 and 113
+// With one tile of keys there is nothing to split (8 heads of 40 tokens, d = 80:
+// 12.2 and 14.8).
+static bool prefill_f32_split(int d, int n_split, int keys, bool cached) {
+  if (keys <= PF_BK) return false;
+  if (d == 64) return n_split <= (cached || keys < 512 ? 512 : keys < 1000 ? 768 : 1024);
+  return n_split <= (keys < 256 ? 256 : cached || keys < 800 ? 512 : 768);
+}
 template <int D, bool CACHED>
 __device__ __forceinline__ void prefill_f32_split_body(
     const float* __restrict__ q, const float* __restrict__ k, const float* __restrict__ v,
@@ -1250,17 +1268,20 @@ static int launch_prefill(const void* q, const void* k, const void* v, void* o, 
         static_cast<const T*>(q), static_cast<const T*>(k), static_cast<const T*>(v),
         static_cast<T*>(o), H, L, qs, kvs, os, scale * PF_LOG2E, vu, L_meta, list, count, info,
         n_qt, L_pad, n_work, cc);
-  } else if (n_work <= PF_ONE_PER_CU) {
-    const int n_split = b * H * ((L + 31) / 32);  // at most four times n_work
-    prefill_f32_split_kernel<D, CACHED><<<n_split, 256, 0, stream>>>(
-        static_cast<const T*>(q), static_cast<const T*>(k), static_cast<const T*>(v),
-        static_cast<T*>(o), H, L, qs, kvs, os, scale * PF_LOG2E, vu, L_meta, list, count, n_qt,
-        L_pad, n_split, cc);
-  } else
-    prefill_attn_kernel_f32<D, CACHED><<<n_work, PF_THREADS, 0, stream>>>(
-        static_cast<const T*>(q), static_cast<const T*>(k), static_cast<const T*>(v),
-        static_cast<T*>(o), H, L, qs, kvs, os, scale * PF_LOG2E, vu, L_meta, list, count, info,
-        n_qt, L_pad, n_work, cc);
+  } else {
+    const int64_t n_split = (int64_t)b * H * ((L + 31) / 32);  // at most four times n_work
+    if (n_work <= PF_ONE_PER_CU &&
+        prefill_f32_split(D, (int)n_split, CACHED ? cc.L_cap : L, CACHED))
+      prefill_f32_split_kernel<D, CACHED><<<(int)n_split, 256, 0, stream>>>(
+          static_cast<const T*>(q), static_cast<const T*>(k), static_cast<const T*>(v),
+          static_cast<T*>(o), H, L, qs, kvs, os, scale * PF_LOG2E, vu, L_meta, list, count, n_qt,
+          L_pad, (int)n_split, cc);
+    else
+      prefill_attn_kernel_f32<D, CACHED><<<n_work, PF_THREADS, 0, stream>>>(
+          static_cast<const T*>(q), static_cast<const T*>(k), static_cast<const T*>(v),
+          static_cast<T*>(o), H, L, qs, kvs, os, scale * PF_LOG2E, vu, L_meta, list, count, info,
+          n_qt, L_pad, n_work, cc);
+  }
   return hip_check(hipGetLastError(), "span_masked_prefill_attn: launch");
 }
 

@@ -216,6 +216,28 @@ def test_prefill_rounds_alike_in_every_launch(d, H, L, many):
     assert float((few.double() - all_[:, :H].double()).abs().max()) <= TOL
 
 
+# fp32: the keys split over the waves (32 query rows a workgroup) on one side of
+# each line, 128 rows on the other (one tile of keys, many workgroups)
+@pytest.mark.parametrize("d,H,L", [(64, 3, 64), (80, 3, 64), (64, 3, 65), (80, 3, 65),
+                                   (64, 73, 200), (64, 74, 200), (80, 36, 200), (80, 37, 200),
+                                   (80, 73, 256), (64, 130, 200), (80, 130, 200), (64, 24, 1000)])
+def test_prefill_f32_launches(d, H, L):
+    print(f"prefill f32 d={d} H={H} L={L}", flush=True)
+    rng = np.random.default_rng(L + d)
+    spans = [W().spans_uniform_lengths(L, 0.4, 4, 40, rng)]
+    q, k, v = (rnd((1, H, L, d), 330 + i, "f32") for i in range(3))
+    k[:, :, L // 2] *= 8
+    o = torch.full_like(q, float("nan"))
+    P().prefill_layer(q, k, v, o, P().SpanMeta(spans, L, DEV), P().Workspace(1, H, L, 1, d, DEV), L)
+    torch.cuda.synchronize()
+    assert torch.isfinite(o).all()
+    heads = sorted({0, 1, H // 2, H - 1})
+    Q, K, V, Og = (f64(x)[0][heads] for x in (q, k, v, o))
+    ref = O.masked_attention(Q, K, V, O.attention_mask(O.token_types(spans[0], L)))
+    # 32-bit sums and exponentials of weights that add to 1, values below 5
+    assert np.abs(Og - ref).max() <= 1e-5, np.abs(Og - ref).max()
+
+
 # groups of waves, a single group; fp32 with 32 query rows a workgroup and 128
 @pytest.mark.parametrize("dtype,d,H", [("bf16", 80, 2), ("bf16", 64, 2), ("bf16", 80, 140),
                                        ("bf16", 64, 270), ("f32", 80, 2), ("f32", 64, 2),
