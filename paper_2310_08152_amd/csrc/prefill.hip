@@ -72,13 +72,19 @@ constexpr int PF_ONE_PER_CU = 256, PF_TWO_PER_CU = 512;
 // d = 64 two (8 of 9216 96.0 and 73.2; 8 of 12288 130 and 110, 80% freed 60.0
 // and 56.6; but 8 of 16384, 80% freed, 84.6 and 85.3).  Not over a cache,
 // where a launch's blocks all see as much (blocks of 512 tokens 1171 and 1286
-// a prompt).
+// a prompt).  There two groups a workgroup (d = 64) need tiles to share beyond
+// one workgroup per CU: over a cache of 300 rows 16 x 32 blocks of 128 tokens
+// take 17.7 with one and 19.0 with two, 8 x 32 of 256 14.6 and 15.7; of 600 rows
+// 25.5 and 24.9, 22.6 and 21.5; of 1000 rows 33.5 and 33.8, 31.3 and 30.5; of
+// 2700 rows 89.6 and 84.5, 68.9 and 64.2.
 constexpr int PF_LONG = 1536;  // list entries from which four groups have tiles enough
+constexpr int PF_LONG_CACHE = 512;
 constexpr int PF_FEW_SLICES = 8, PF_THREE_PER_CU = 768;
 static int prefill_groups(int d, int n_work, int L_pad, int slices, bool cached) {
   const bool few = !cached && slices <= PF_FEW_SLICES;
   if (d == 80) return n_work <= (few ? PF_TWO_PER_CU : PF_ONE_PER_CU) ? 3 : 1;
-  if (n_work <= PF_ONE_PER_CU && L_pad >= PF_LONG) return 4;
+  if (n_work <= PF_ONE_PER_CU) return L_pad >= PF_LONG ? 4 : 2;
+  if (cached && L_pad < PF_LONG_CACHE) return 1;
   return n_work <= (few ? PF_THREE_PER_CU : PF_TWO_PER_CU) ? 2 : 1;
 }
 constexpr uint32_t PF_NONE = 0x00ffffffu;  // list entry of a padding column

@@ -238,6 +238,36 @@ def test_prefill_f32_launches(d, H, L):
     assert np.abs(Og - ref).max() <= 1e-5, np.abs(Og - ref).max()
 
 
+# over a cache: one group of waves (many workgroups), two (d = 64, up to 512 where
+# the cache is long) and four (d = 64, few over 1536 rows and more), three (d = 80,
+# few); fp32 with the keys split and with 128 rows a workgroup
+@pytest.mark.parametrize("dtype,d,H,L,block", [
+    ("bf16", 80, 130, 450, 200), ("bf16", 80, 2, 450, 200), ("bf16", 64, 260, 450, 200),
+    ("bf16", 64, 130, 450, 200), ("bf16", 64, 2, 450, 200), ("bf16", 64, 2, 1900, 300),
+    ("bf16", 64, 130, 630, 200), ("f32", 64, 130, 300, 130), ("f32", 64, 5, 300, 130),
+    ("f32", 80, 130, 300, 130), ("f32", 80, 5, 300, 130)])
+def test_prefill_block_launches(dtype, d, H, L, block):
+    """Blocks with a ragged last one, spans freed between them and one that
+    stays open across them, against the oracle over the whole prompt."""
+    print(f"blocks {dtype} d={d} H={H} L={L} block={block}", flush=True)
+    rng = np.random.default_rng(L + d + H)
+    a = block - 30
+    spans = [[(c, r) for c, r in W().spans_uniform_lengths(a - 1, 0.4, 4, 24, rng)]
+             + [(a, a + 60), (a + 61, L + 2)]]
+    meta = P().SpanMeta(spans, L + 4, DEV)
+    q, k, v = (rnd((1, 1, H, L, d), 350 + i, dtype) for i in range(3))
+    o = torch.full_like(q, float("nan"))
+    cache = P().KVCache(1, 1, H, L, d, q.dtype, DEV)
+    P().prefill_progressive(q, k, v, o, cache, meta, P().Workspace(1, H, 1, L, d, DEV, block=block),
+                            L, block)
+    torch.cuda.synchronize()
+    assert int(cache.status) == 0 and torch.isfinite(o).all()
+    heads = sorted({0, 1, H // 2, H - 1})
+    Q, K, V, Og = (f64(x)[0, 0][heads] for x in (q, k, v, o))
+    ref = O.masked_attention(Q, K, V, O.attention_mask(O.token_types(spans[0], L)))
+    assert np.abs(Og - ref).max() <= (TOL if dtype == "bf16" else 1e-5), np.abs(Og - ref).max()
+
+
 # groups of waves, a single group; fp32 with 32 query rows a workgroup and 128
 @pytest.mark.parametrize("dtype,d,H", [("bf16", 80, 2), ("bf16", 64, 2), ("bf16", 80, 140),
                                        ("bf16", 64, 270), ("f32", 80, 2), ("f32", 64, 2),
