@@ -64,6 +64,21 @@ constexpr int PF_GROUP = 8;
 // With more workgroups each waits for a whole CU: 1024 of d = 64 36.2 and 38.1
 // (two), 512 of d = 80 17.8 and 22.1 (4 sequences of 512 tokens, three).
 constexpr int PF_ONE_PER_CU = 256, PF_TWO_PER_CU = 512;
+// A short list has no tiles to share, and larger workgroups start and merge
+// slower.  The host knows the prompt's tokens (or the cache's rows), of which
+// the spans may free most.  One group and so, nothing / half / 80% freed:
+//   d = 80: 40 tokens 5.8 and 8.0 (three), 128 7.7 / 8.1 / 8.2 and 9.3 / 10.1 /
+//     10.1; 2 sequences of 256 10.2 / 10.8 / 9.7 and 11.4 / 11.8 / 10.9, of 512
+//     15.3 / 12.4 / 11.0 and 13.8 / 12.4 / 12.0
+//   d = 64, up to one workgroup per CU: 40 tokens 5.5 and 6.4 (two); 4 sequences
+//     of 192 8.3 / 8.3 / 8.6 and 8.7 / 8.7 / 9.0, of 256 10.4 / 10.7 / 9.9 and
+//     9.9 / 10.2 / 10.3
+//   d = 64, beyond: 16 sequences of 40 tokens 6.0 and 8.1, 4 of 320 12.0 / 12.0 /
+//     11.1 and 13.1 / 12.9 / 12.1, of 512 18.3 / 15.5 / 13.1 and 17.9 / 15.8 /
+//     14.1; over caches of 300 rows 16 x 32 blocks of 128 tokens 17.7 and 19.0,
+//     of 600 rows 25.5 and 24.9, of 2700 rows 89.6 and 84.5
+constexpr int PF_SHARE_80 = 512, PF_SHARE_64 = 256, PF_SHARE_64_TWO = 512;
+constexpr int PF_LONG = 1409;  // tokens or rows from which four groups have tiles enough
 // Few slices are long ones, whose heaviest blocks outlast the rest of the
 // launch: with at most eight, up to 512 workgroups of d = 80 take three groups
 // too (8 heads of 8192 tokens, half freed, 87.7 and 69.5; 80% freed 42.7 and
@@ -72,20 +87,14 @@ constexpr int PF_ONE_PER_CU = 256, PF_TWO_PER_CU = 512;
 // d = 64 two (8 of 9216 96.0 and 73.2; 8 of 12288 130 and 110, 80% freed 60.0
 // and 56.6; but 8 of 16384, 80% freed, 84.6 and 85.3).  Not over a cache,
 // where a launch's blocks all see as much (blocks of 512 tokens 1171 and 1286
-// a prompt).  There two groups a workgroup (d = 64) need tiles to share beyond
-// one workgroup per CU: over a cache of 300 rows 16 x 32 blocks of 128 tokens
-// take 17.7 with one and 19.0 with two, 8 x 32 of 256 14.6 and 15.7; of 600 rows
-// 25.5 and 24.9, 22.6 and 21.5; of 1000 rows 33.5 and 33.8, 31.3 and 30.5; of
-// 2700 rows 89.6 and 84.5, 68.9 and 64.2.
-constexpr int PF_LONG = 1536;  // list entries from which four groups have tiles enough
-constexpr int PF_LONG_CACHE = 512;
+// a prompt).
 constexpr int PF_FEW_SLICES = 8, PF_THREE_PER_CU = 768;
-static int prefill_groups(int d, int n_work, int L_pad, int slices, bool cached) {
+static int prefill_groups(int d, int n_work, int keys, int slices, bool cached) {
   const bool few = !cached && slices <= PF_FEW_SLICES;
-  if (d == 80) return n_work <= (few ? PF_TWO_PER_CU : PF_ONE_PER_CU) ? 3 : 1;
-  if (n_work <= PF_ONE_PER_CU) return L_pad >= PF_LONG ? 4 : 2;
-  if (cached && L_pad < PF_LONG_CACHE) return 1;
-  return n_work <= (few ? PF_THREE_PER_CU : PF_TWO_PER_CU) ? 2 : 1;
+  if (d == 80)
+    return keys >= PF_SHARE_80 && n_work <= (few ? PF_TWO_PER_CU : PF_ONE_PER_CU) ? 3 : 1;
+  if (n_work <= PF_ONE_PER_CU) return keys >= PF_LONG ? 4 : keys >= PF_SHARE_64 ? 2 : 1;
+  return keys >= PF_SHARE_64_TWO && n_work <= (few ? PF_THREE_PER_CU : PF_TWO_PER_CU) ? 2 : 1;
 }
 constexpr uint32_t PF_NONE = 0x00ffffffu;  // list entry of a padding column
 constexpr float PF_LOG2E = 1.4426950408889634f;
@@ -1262,7 +1271,7 @@ static int launch_prefill(const void* q, const void* k, const void* v, void* o, 
   }
   const int n_work = b * H * n_qt;
   if constexpr (sizeof(T) == 2) {
-    const int groups = prefill_groups(D, n_work, L_pad, b * H, CACHED);
+    const int groups = prefill_groups(D, n_work, CACHED ? cc.L_cap : L, b * H, CACHED);
     auto kernel = prefill_attn_kernel_bf16<D, CACHED, 1>;
     if constexpr (D == 64) {
       if (groups == 2) kernel = prefill_attn_kernel_bf16<D, CACHED, 2>;

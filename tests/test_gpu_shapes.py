@@ -169,9 +169,12 @@ def test_span_metadata_plan_and_scan_round_sizes(L):
 
 # one workgroup's tiles shared among groups of waves (few workgroups: three
 # groups at d = 80, two or, for long lists, four at d = 64), with fewer tiles
-# than groups, as many, and a remainder; one group (many workgroups); and three
+# than groups (the first blocks), as many, and a remainder; one group (short
+# prompts, many workgroups), on both sides of each line; and three
 # (d = 80) or two (d = 64) in more workgroups where the slices are few and long
 @pytest.mark.parametrize("d,H,L", [(80, 2, 1), (80, 2, 64), (80, 2, 130), (80, 2, 400), (80, 3, 901),
+                                   (80, 2, 511), (80, 2, 512), (64, 2, 255), (64, 2, 256),
+                                   (64, 2, 1408), (64, 2, 1409), (64, 70, 511), (64, 70, 512),
                                    (64, 2, 1), (64, 2, 65), (64, 2, 700), (64, 2, 1600),
                                    (80, 140, 129), (64, 260, 129), (80, 48, 700), (64, 96, 700),
                                    (80, 8, 4224), (64, 8, 8320)])
@@ -242,7 +245,7 @@ def test_prefill_f32_launches(d, H, L):
 # the cache is long) and four (d = 64, few over 1536 rows and more), three (d = 80,
 # few); fp32 with the keys split and with 128 rows a workgroup
 @pytest.mark.parametrize("dtype,d,H,L,block", [
-    ("bf16", 80, 130, 450, 200), ("bf16", 80, 2, 450, 200), ("bf16", 64, 260, 450, 200),
+    ("bf16", 80, 130, 630, 200), ("bf16", 80, 2, 630, 200), ("bf16", 64, 260, 450, 200),
     ("bf16", 64, 130, 450, 200), ("bf16", 64, 2, 450, 200), ("bf16", 64, 2, 1900, 300),
     ("bf16", 64, 130, 630, 200), ("f32", 64, 130, 300, 130), ("f32", 64, 5, 300, 130),
     ("f32", 80, 130, 300, 130), ("f32", 80, 5, 300, 130)])
@@ -276,7 +279,7 @@ def test_prefill_reads_only_its_rows(dtype, d, H):
     """Rows behind the prompt's, within the stride to the next slice, are not
     read, even where a longer prompt's plan lists them."""
     print(f"prefill rows {dtype} d={d} H={H}", flush=True)
-    L, room = 200, 256
+    L, room = 600, 640
     meta = P().SpanMeta([[(3, 40)]], room, DEV)
     ws = P().Workspace(1, H, room, 1, d, DEV)
     q = rnd((1, H, L, d), 340, dtype)
