@@ -10,7 +10,10 @@
 //          in place and emits kept_src_row.  Bound by the round trips to
 //          memory of its chunks, which follow one another: a chunk is 4096
 //          rows (16 waves, 4 rows a thread in flight together; 4096 rows take
-//          5.4 us, in chunks of 256 rows they took 19.2).
+//          5.4 us, in chunks of 256 rows they took 19.2).  Small caches are
+//          one chunk of 4 waves, whose counts every wave adds up by itself
+//          (up to 256 rows of one row a thread 0.9 us less than the larger
+//          workgroup, up to 1024 rows of four 0.4 us less).
 //   move : one workgroup per (layer, k/v, sequence, head) slice; moves the
 //          surviving rows to their new index, 16 bytes per lane, in chunks
 //          that read everything before writing anything.  A row never moves
@@ -20,13 +23,11 @@
 
 namespace sckv {
 
-constexpr int SCAN_WAVES = 16;
-constexpr int SCAN_THREADS = 64 * SCAN_WAVES;
-constexpr int SCAN_U = 4;  // rows per thread of a chunk
-static_assert(SCAN_WAVES * SCAN_U == 64, "one wave scans the chunk's counts");
 constexpr int MOVE_THREADS = 256;
 
-__global__ __launch_bounds__(SCAN_THREADS) void compact_scan_kernel(
+// chunks of U rows a thread
+template <int WAVES, int U>
+__global__ __launch_bounds__(64 * WAVES) void compact_scan_kernel(
     int32_t* __restrict__ kv_len, int32_t* __restrict__ tok_idx, int32_t* __restrict__ pos_ids,
     const int32_t* __restrict__ next_tok, const int32_t* __restrict__ vu, int32_t L_meta,
     int32_t L_cap, int32_t* __restrict__ kept_src) {
@@ -34,9 +35,12 @@ __global__ __launch_bounds__(SCAN_THREADS) void compact_scan_kernel(
   const int tid = threadIdx.x;
   const int wave = tid >> 6;
   const int lane = tid & 63;
-  // kept rows before (pass u, wave w) of the chunk at [u * SCAN_WAVES + w];
-  // the chunk's total behind them
-  __shared__ int before[64 + 1];
+  constexpr int THREADS = 64 * WAVES;
+  constexpr int COUNTS = WAVES * U;
+  static_assert(COUNTS <= 64, "one wave scans the chunk's counts");
+  // kept rows of (pass u, wave w) of the chunk, then those before it, at
+  // [u * WAVES + w]; the chunk's total behind them
+  __shared__ int before[COUNTS + 1];
   int n_old = kv_len[s];
   n_old = n_old < 0 ? 0 : (n_old > L_cap ? L_cap : n_old);
   const int P = next_tok[s];
@@ -45,54 +49,68 @@ __global__ __launch_bounds__(SCAN_THREADS) void compact_scan_kernel(
   int32_t* ks = kept_src + (int64_t)s * L_cap;
   const int32_t* vus = vu + (int64_t)s * L_meta;
   int carry = 0;
-  for (int base = 0; base < n_old; base += SCAN_U * SCAN_THREADS) {
-    int t[SCAN_U], p[SCAN_U];
-    uint64_t m[SCAN_U];
-    bool keep[SCAN_U];
+  for (int base = 0; base < n_old; base += U * THREADS) {
+    int t[U], p[U];
+    uint64_t m[U];
+    bool keep[U];
 #pragma unroll
-    for (int u = 0; u < SCAN_U; ++u) {
-      const int row = base + u * SCAN_THREADS + tid;
+    for (int u = 0; u < U; ++u) {
+      const int row = base + u * THREADS + tid;
       t[u] = row < n_old ? tok[row] : 0;
       p[u] = row < n_old ? pp[row] : 0;
     }
 #pragma unroll
-    for (int u = 0; u < SCAN_U; ++u) {
+    for (int u = 0; u < U; ++u) {
       const bool known = t[u] >= 0 && t[u] < L_meta;
       const int v = known ? vus[t[u]] : 0;
-      keep[u] = base + u * SCAN_THREADS + tid < n_old && (!known || (v != t[u] && v >= P));
+      keep[u] = base + u * THREADS + tid < n_old && (!known || (v != t[u] && v >= P));
     }
     wait_vmem();  // every read of this chunk has landed before any write below
 #pragma unroll
-    for (int u = 0; u < SCAN_U; ++u) {
+    for (int u = 0; u < U; ++u) {
       m[u] = __ballot(keep[u]);
-      if (lane == 0) before[u * SCAN_WAVES + wave] = __popcll(m[u]);
+      if (lane == 0) before[u * WAVES + wave] = __popcll(m[u]);
     }
     __syncthreads();
-    if (wave == 0) {  // exclusive prefix sum of the 64 counts
-      const int c = before[lane];
-      int sum = c;
+    int first[U], total = 0;  // kept rows before this wave's of each pass
+    if constexpr (COUNTS <= 16) {  // few counts: every wave adds them up
 #pragma unroll
-      for (int off = 1; off < 64; off <<= 1) {
-        const int x = __shfl_up(sum, off, 64);
-        if (lane >= off) sum += x;
+      for (int u = 0; u < U; ++u)
+#pragma unroll
+        for (int w = 0; w < WAVES; ++w) {
+          if (w == wave) first[u] = total;
+          total += before[u * WAVES + w];
+        }
+    } else {
+      if (wave == 0) {  // exclusive prefix sum
+        const int c = lane < COUNTS ? before[lane] : 0;
+        int sum = c;
+#pragma unroll
+        for (int off = 1; off < 64; off <<= 1) {
+          const int x = __shfl_up(sum, off, 64);
+          if (lane >= off) sum += x;
+        }
+        if (lane < COUNTS) before[lane] = sum - c;
+        if (lane == 63) before[COUNTS] = sum;
       }
-      before[lane] = sum - c;
-      if (lane == 63) before[64] = sum;
-    }
-    __syncthreads();
+      __syncthreads();
 #pragma unroll
-    for (int u = 0; u < SCAN_U; ++u) {
+      for (int u = 0; u < U; ++u) first[u] = before[u * WAVES + wave];
+      total = before[COUNTS];
+    }
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
       if (keep[u]) {
-        const int rank = carry + before[u * SCAN_WAVES + wave] + mask_rank(m[u]);
+        const int rank = carry + first[u] + mask_rank(m[u]);
         tok[rank] = t[u];
         pp[rank] = p[u];
-        ks[rank] = base + u * SCAN_THREADS + tid;
+        ks[rank] = base + u * THREADS + tid;
       }
     }
-    carry += before[64];
+    carry += total;
     __syncthreads();
   }
-  for (int r = carry + tid; r < L_cap; r += SCAN_THREADS) ks[r] = -1;
+  for (int r = carry + tid; r < L_cap; r += THREADS) ks[r] = -1;
   __syncthreads();  // every thread has read kv_len[s]
   if (tid == 0) kv_len[s] = carry;
 }
@@ -186,8 +204,11 @@ extern "C" int kv_compact(void* kv, void* kv_out, int32_t M, int32_t b, int32_t 
     return fail(SCKV_EINVAL, "kv_compact: cache buffers must be 16-byte aligned");
   const int64_t slices = (int64_t)M * 2 * b * H;
   if (slices > 0x7fffffff) return fail(SCKV_EUNSUP, "kv_compact: too many slices");
-  compact_scan_kernel<<<b, SCAN_THREADS, 0, stream>>>(kv_len, tok_idx, pos_ids, next_tok, vu,
-                                                      L_meta, L_cap, kept_src_row);
+  auto scan = L_cap <= 256    ? compact_scan_kernel<4, 1>
+              : L_cap <= 1024 ? compact_scan_kernel<4, 4>
+                              : compact_scan_kernel<16, 4>;
+  scan<<<b, L_cap <= 1024 ? 256 : 1024, 0, stream>>>(kv_len, tok_idx, pos_ids, next_tok, vu, L_meta,
+                                                     L_cap, kept_src_row);
   int rc = hip_check(hipGetLastError(), "kv_compact: scan launch");
   if (rc) return rc;
   const int rowb = d_head * elem_bytes(dt);

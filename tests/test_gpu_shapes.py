@@ -134,11 +134,11 @@ def test_decode_splits_long_slices(slices, L_cap, one, d):
         assert np.abs(Og[s] - ref).max() <= TOL, s
 
 
-@pytest.mark.parametrize("L", [1, 1023, 1025, 4096, 4097, 9000])
+@pytest.mark.parametrize("L", [1, 255, 256, 1023, 1024, 1025, 4096, 4097, 9000])
 def test_span_metadata_plan_and_scan_round_sizes(L):
     """Span metadata, compaction indices and (through the attention's last
     rows) the prompt's plan at the edges of their rounds (256 tokens a
-    workgroup, 1024 columns and 4096 rows a round)."""
+    workgroup, 1024 columns and 256, 1024 or 4096 rows a round)."""
     print(f"meta, plan, scan L={L}", flush=True)
     rng = np.random.default_rng(L)
     spans = [W().spans_uniform_lengths(L, 0.5, 2, 25, rng) if L > 60 else [], [(0, L + 3)]]
