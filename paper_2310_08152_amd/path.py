@@ -67,12 +67,14 @@ class KVCache:
         pos = meta.pos
         if (pos.is_cuda and pos.device == self.kv_len.device and pos.dtype == torch.int32
                 and pos.dim() == 2 and pos.is_contiguous() and pos.shape[0] == self.b
-                and 0 < L <= min(self.L_cap, pos.shape[1])):
+                and 0 < L <= min(self.L_cap, pos.shape[1])
+                and pos.device.index == torch.cuda.current_device()):
             B.kv_start(self.kv_len, self.tok_idx, self.pos_ids, self.cur_tok, pos, pos.shape[1], L,
                        self.b, self.L_cap)
             return
         # an empty prompt, one sequence's positions for all, positions of another
-        # type, layout or device, a cache on the host, or sizes torch refuses
+        # type, layout or device, a cache on the host or on a GPU that is not the
+        # current one (which a launch goes to), or sizes torch refuses
         self.tok_idx[:, :L] = torch.arange(L, dtype=torch.int32, device=self.kv.device)
         self.pos_ids[:, :L] = meta.pos[:, :L]
         self.kv_len.fill_(L)

@@ -94,3 +94,31 @@ def test_start_prompt_takes_any_positions(dev, form):
         assert torch.equal(cache.pos_ids.cpu(), want)
         assert cache.tok_idx[:, :5].tolist() == [[0, 1, 2, 3, 4]] * 3
         assert cache.kv_len.tolist() == cache.cur_tok.tolist() == [5] * 3
+
+
+@pytest.mark.parametrize("current", [0, 1])
+def test_start_prompt_on_another_gpu(monkeypatch, current):
+    """The library launches on the current device: a cache on another GPU is
+    filled by torch's copies, which go to the cache's.  (Stand-ins on the CPU
+    for tensors on the second GPU.)"""
+    from paper_2310_08152_amd import path as P
+    gpu = torch.device("cuda:1")
+    pos = torch.arange(24, dtype=torch.int32).view(2, 12)
+
+    class OnGpu:
+        is_cuda, device, dtype, shape = True, gpu, pos.dtype, pos.shape
+        dim, is_contiguous = pos.dim, pos.is_contiguous
+
+        def __getitem__(self, at):
+            return pos[at]
+
+    cache = P.KVCache(1, 2, 1, 10, 64, torch.float32, "cpu")
+    length = cache.kv_len
+    cache.kv_len = SimpleNamespace(device=gpu, fill_=length.fill_)
+    launches = []
+    monkeypatch.setattr(torch.cuda, "current_device", lambda: current)
+    monkeypatch.setattr(P.B, "kv_start", lambda *a: launches.append(a))
+    cache.start_prompt(5, SimpleNamespace(pos=OnGpu()))
+    assert len(launches) == current
+    if not current:
+        assert torch.equal(cache.pos_ids[:, :5], pos[:, :5]) and length.tolist() == [5, 5]
