@@ -97,7 +97,7 @@ class KVCache:
                     meta.L_meta, self.b, self.L_cap, self.status, stream=stream)
 
 
-DECODE_PARTIALS = 1024  # chunk partials a decode workspace holds at least
+DECODE_PARTIALS = 512  # chunk partials a decode workspace holds at least
 
 
 class Workspace:
@@ -107,9 +107,9 @@ class Workspace:
     def __init__(self, b: int, H: int, L: int, L_cap: int, d: int, device, block: int = 0):
         self.prefill = torch.empty(max(1, B.sckv_prefill_workspace_bytes(b, max(L, 1))),
                                    dtype=torch.uint8, device=device)
-        # room for as many partials as a launch of few slices splits into
-        # (512 workgroups and a remainder), which is more than the least the
-        # library accepts where the cache is short
+        # room for as many partials as a launch of few slices splits into (512
+        # workgroups), which is more than the least the library accepts where
+        # the cache is short
         self.decode = torch.empty(max(1, B.sckv_decode_workspace_bytes(b, H, L_cap, d),
                                       DECODE_PARTIALS * (d + 2) * 4),
                                   dtype=torch.uint8, device=device)
