@@ -325,9 +325,10 @@ int kv_compact(void* kv, void* kv_out, int32_t M, int32_t b, int32_t H, int32_t 
  * status : nullable int32, status bits OR-ed in.
  * Launch shape: with b*H >= 512 slices, and bf16 with fewer over caches of
  * at most min(512 + 8 * b*H, 1536) rows: one workgroup per (sequence, head)
- * covers all its rows and writes o (the workspace is not touched).  Otherwise the rows are cut into balanced chunks of at most about
- * 1024 rows, one workgroup each, and a second kernel merges the chunk
- * partials (log-sum-exp) into o.  bf16 scores are computed on the matrix cores with
+ * covers all its rows and writes o (the workspace is not touched).
+ * Otherwise the rows are cut into balanced chunks of at most about 1024
+ * rows, one workgroup each, and a second kernel merges the chunk partials
+ * (log-sum-exp) into o.  bf16 scores are computed on the matrix cores with
  * q carried as two bf16 terms (about fp32 accuracy).
  * ------------------------------------------------------------------------- */
 size_t sckv_decode_workspace_bytes(int32_t b, int32_t H, int32_t L_cap, int32_t d_head);

@@ -144,9 +144,6 @@ __device__ __forceinline__ int step_kind(const int32_t* cur_tok, const int32_t* 
   return 0;
 }
 
-// Writes the final output of a slice whose step is not an ordinary append
-// (kind 1: <CL>, the output is v_new; kind 2/3: failure, NaN and a status
-// bit).  `tid` runs over `nthr` threads.
 // A slice's rows split into n chunks of `rows` rows (the last one shorter).
 // Chunk starts are multiples of 16 rows:
 // a wave then reads whole 128-byte lines (a bf16 row of 80 elements is 160
@@ -175,6 +172,9 @@ __device__ __forceinline__ ChunkPlan chunk_plan(int rows, Split sp) {
   return p;
 }
 
+// Writes the final output of a slice whose step is not an ordinary append
+// (kind 1: <CL>, the output is v_new; kind 2/3: failure, NaN and a status
+// bit).  `tid` runs over `nthr` threads.
 template <typename T, int D>
 __device__ __forceinline__ void write_special(int kind, const T* v_new, T* o, int32_t* status,
                                               int bh, int H, int tid, int nthr) {

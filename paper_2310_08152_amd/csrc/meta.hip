@@ -138,7 +138,8 @@ __device__ __forceinline__ void rope_body(const T* x, T* y, int32_t b, int32_t H
         for (int e = 0; e < E; ++e) {
           const float x1 = fa[e], x2 = fc[e];
           // the fused forms are written out: which product of a pair stays
-          // unrounded is then the same in every kernel
+          // unrounded is then the same in this file's kernels (the decode
+          // step, which turns one key, leaves it to the compiler)
           fa[e] = fmaf(x1, cs[e], -(x2 * sn[e]));
           fc[e] = fmaf(x2, cs[e], x1 * sn[e]);
         }

@@ -528,8 +528,9 @@ __device__ __forceinline__ void prefill_attn_body(
   // the LDS block address in scalar registers.  The descriptor ends with the
   // last row, not with the stride to the next slice: behind the last slice's
   // rows the buffer may end, and what is read past the descriptor (the last
-  // row's pad slot, rows of a plan made for a longer prompt) is zero instead.  Each lane's tile row and piece offset per round are fixed
-  // for the kernel and computed once here.
+  // row's pad slot, rows of a plan made for a longer prompt) is zero instead.
+  // Each lane's tile row and piece offset per round are fixed for the kernel
+  // and computed once here.
   const int wave_s = __builtin_amdgcn_readfirstlane(wave);
   const int slice_bytes = (CACHED ? cc.L_cap : L) * D * (int)sizeof(T);
   const __amdgpu_buffer_rsrc_t krs =
