@@ -654,13 +654,15 @@ __device__ __forceinline__ void prefill_attn_body(
   // summary of the tile being computed, read from the ring one step early
   // so that the step starts with its key reads
   TileInfo tcur;
-  // The loop is bound by vector issue and by the matrix instructions' share of
-  // it (SQ counters at d = 64: vector instructions active 70% of the CU-busy
-  // clocks, matrix cores busy 50%), so instructions count: the running maximum
-  // is kept in the form its users take, and an element mask is one unsigned
-  // compare of a difference (3 vector instructions an element instead of 4
-  // and a scalar one).  2-4% of a layer at either head size (16 x 4096 tokens,
-  // d = 80: 1011 -> 988 us; 8 x 2048, d = 64: 120.4 -> 117.5), bit for bit.
+  // Neither unit is full: vector issue is the busier one (SQ counters over a
+  // launch: vector instructions active 66% of the clocks and matrix cores busy
+  // 50% at 16384 tokens, d = 64; 50 and 41% at 16 x 4096, d = 80), and a wave's
+  // dependent steps, which three or four waves a SIMD cover in part, take the
+  // rest.  Instructions shorten that chain too: the running maximum is kept in
+  // the form its users take, and an element mask is one unsigned compare of a
+  // difference (3 vector instructions an element instead of 4 and a scalar
+  // one).  2-4% of a layer at either head size (16 x 4096 tokens, d = 80: 1011
+  // -> 988 us; 8 x 2048, d = 64: 120.4 -> 117.5), bit for bit.
   // A 64-key tile is weighed in softmax steps of NB 32-key blocks: scores
   // of the step, its online softmax, its share of the value product.  At
   // D = 64 a step is one block (32 keys), so only half a tile's scores and
