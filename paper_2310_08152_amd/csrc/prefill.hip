@@ -1027,23 +1027,33 @@ __global__ __launch_bounds__(PF_THREADS) void prefill_attn_kernel_f32(
 // waves' partial outputs are merged through LDS.  It stages every tile four
 // times as often for the same rows, so it is for launches that leave CUs idle
 // (4 heads of 256 tokens, d = 64: 29.5 us with 128 rows a workgroup, 16.0 us so).
-// A CU holds two such workgroups at d = 64, one at d = 80 (73 and 98 KB of LDS):
-// the line is at one round of them, at d = 80 at two where there are tiles
-// enough to split, and at more for long prompts, whose light blocks leave room
-// (over a cache all blocks see as much).  us with 128 rows a workgroup and so:
-//   d = 64: 128 heads of 128 tokens (512 workgroups) 19.6 and 18.6, 64 of 256
-//     30.2 and 20.8; 96 of 256 (768) 30.6 and 39.0; 48 of 512 (768) 46.7 and
-//     43.0, 64 of 512 (1024) 45.9 and 49.6; 32 of 1000 (1024) 72.4 and 68.6; 64
-//     of 512 over a cache of 1500 rows (1024) 136 and 143
-//   d = 80: 64 heads of 128 tokens (256 workgroups) 23.4 and 15.5, 96 of 128
-//     (384) 23.8 and 28.9; 64 of 256 (512) 37.2 and 33.9, 48 of 512 (768) 59.1
-//     and 63.5; 16 of 1500 (752) 125 and 113, 32 of 1000 (1024) 92.5 and 113
+// A CU holds two such workgroups at d = 64, one at d = 80 (73 and 98 KB of LDS).
+// The line is at one round of them, further for long prompts or caches, whose
+// light blocks leave room, and nearer for short blocks over few keys; it is drawn
+// where neither nothing freed nor 60% is slower.  us with 128 rows a workgroup and
+// so, nothing freed and 60%:
+//   d = 64: 128 heads of 128 tokens (512 workgroups) 18.9 / 19.5 and 18.2 / 19.1,
+//     64 of 256 28.9 / 29.5 and 20.6 / 21.2; of 65 tokens 96 (288) 16.2 / 16.6 and
+//     13.7 / 14.8, 128 (384) 16.3 / 16.8 and 17.1 / 18.1; 192 blocks of 64 over 320
+//     rows (384) 33.3 / 22.4 and 30.6 / 24.6; beyond one round 16 of 1500 (752) 126 /
+//     63.1 and 74.0 / 55.8, 16 of 2048 (1024) 169 / 85.1 and 121 / 79.0, but 32 of 700
+//     (704) 60.9 / 39.8 and 44.9 / 41.3, 32 of 1000 (1024) 88.1 / 49.6 and 74.7 / 54.1
+//   d = 80: 64 heads of 128 tokens (256 workgroups) 22.7 / 23.3 and 14.6 / 15.9; 32 of
+//     512 (512) 61.2 / 43.2 and 42.5 / 39.2, but 48 of 300 (480) 38.7 / 30.4 and 36.9 /
+//     34.1; 64 blocks of 256 over 512 rows (512) 62.1 / 43.4 and 51.8 / 43.5, but 192 of
+//     64 over 320 (384) 43.7 / 28.5 and 47.8 / 38.9; 16 of 1200 (608) 127 / 68.8 and
+//     93.6 / 64.8, 8 of 3000 (752) 309 / 139 and 229 / 122, but 16 of 1500 (752) 163 /
+//     80.0 and 129 / 82.6
 // With one tile of keys there is nothing to split (8 heads of 40 tokens, d = 80:
 // 12.2 and 14.8).
-static bool prefill_f32_split(int d, int n_split, int keys, bool cached) {
+static bool prefill_f32_split(int d, int n_split, int rows, int keys, bool cached) {
   if (keys <= PF_BK) return false;
-  if (d == 64) return n_split <= (cached || keys < 512 ? 512 : keys < 1000 ? 768 : 1024);
-  return n_split <= (keys < 256 ? 256 : cached || keys < 800 ? 512 : 768);
+  if (d == 64) {
+    if (rows < PF_BQ && keys < 512) return n_split <= 320;
+    return n_split <= (cached || keys < 1200 ? 512 : keys < 2048 ? 768 : 1024);
+  }
+  if (keys < (cached ? 512 : 400)) return n_split <= 256;
+  return n_split <= (cached || keys < 1200 ? 512 : keys < 2048 ? 640 : 768);
 }
 template <int D, bool CACHED>
 __device__ __forceinline__ void prefill_f32_split_body(
@@ -1297,7 +1307,7 @@ static int launch_prefill(const void* q, const void* k, const void* v, void* o, 
   } else {
     const int64_t n_split = (int64_t)b * H * ((L + 31) / 32);  // at most four times n_work
     if (n_work <= PF_ONE_PER_CU &&
-        prefill_f32_split(D, (int)n_split, CACHED ? cc.L_cap : L, CACHED))
+        prefill_f32_split(D, (int)n_split, L, CACHED ? cc.L_cap : L, CACHED))
       prefill_f32_split_kernel<D, CACHED><<<(int)n_split, 256, 0, stream>>>(
           static_cast<const T*>(q), static_cast<const T*>(k), static_cast<const T*>(v),
           static_cast<T*>(o), H, L, qs, kvs, os, scale * PF_LOG2E, vu, L_meta, list, count, n_qt,

@@ -223,7 +223,9 @@ def test_prefill_rounds_alike_in_every_launch(d, H, L, many):
 # each line, 128 rows on the other (one tile of keys, many workgroups)
 @pytest.mark.parametrize("d,H,L", [(64, 3, 64), (80, 3, 64), (64, 3, 65), (80, 3, 65),
                                    (64, 73, 200), (64, 74, 200), (80, 36, 200), (80, 37, 200),
-                                   (80, 73, 256), (64, 130, 200), (80, 130, 200), (64, 24, 1000)])
+                                   (80, 73, 256), (64, 130, 200), (80, 130, 200), (64, 24, 1000),
+                                   (64, 80, 127), (64, 81, 127), (80, 39, 400), (80, 40, 400),
+                                   (64, 20, 1200), (80, 16, 1200), (64, 16, 2048), (80, 9, 2100)])
 def test_prefill_f32_launches(d, H, L):
     print(f"prefill f32 d={d} H={H} L={L}", flush=True)
     rng = np.random.default_rng(L + d)
