@@ -75,9 +75,19 @@ constexpr int PF_ONE_PER_CU = 256, PF_TWO_PER_CU = 512;
 //     9.9 / 10.2 / 10.3
 //   d = 64, beyond: 16 sequences of 40 tokens 6.0 and 8.1, 4 of 320 12.0 / 12.0 /
 //     11.1 and 13.1 / 12.9 / 12.1, of 512 18.3 / 15.5 / 13.1 and 17.9 / 15.8 /
-//     14.1; over caches of 300 rows 16 x 32 blocks of 128 tokens 17.7 and 19.0,
-//     of 600 rows 25.5 and 24.9, of 2700 rows 89.6 and 84.5
+//     14.1
 constexpr int PF_SHARE_80 = 512, PF_SHARE_64 = 256, PF_SHARE_64_TWO = 512;
+// Over a cache a block sees the freed rows' room too, and blocks of one
+// workgroup a slice are all as long: beyond one workgroup per CU nothing is left
+// for groups to even out.  Half freed unless stated:
+//   d = 80: 128 single tokens over 513 rows 10.4 and 11.0, over 769 12.8 and 12.6
+//   d = 64, up to one workgroup per CU (40% freed): 32 blocks of 64 tokens over 320
+//     rows 8.1 and 8.6, of 300 over 300 10.2 and 10.4, of 128 over 384 11.7 and 11.2
+//   d = 64, beyond: 512 single tokens over 513 rows 10.9 and 12.8, over 1501 21.3
+//     and 23.4, blocks of 64 over 576 16.1 and 17.9, over 1564 27.3 and 28.1; 128
+//     blocks of 512 (four workgroups each) over 712 19.5 and 20.4, over 1024 23.7
+//     and 22.6, over 3012 46.0 and 41.3
+constexpr int PF_CACHED_80 = 640, PF_CACHED_64 = 384, PF_CACHED_64_TWO = 896;
 constexpr int PF_LONG = 1409;  // tokens or rows from which four groups have tiles enough
 // Few slices are long ones, whose heaviest blocks outlast the rest of the
 // launch: with at most eight, up to 512 workgroups of d = 80 take three groups
@@ -92,9 +102,13 @@ constexpr int PF_FEW_SLICES = 8, PF_THREE_PER_CU = 768;
 static int prefill_groups(int d, int n_work, int keys, int slices, bool cached) {
   const bool few = !cached && slices <= PF_FEW_SLICES;
   if (d == 80)
-    return keys >= PF_SHARE_80 && n_work <= (few ? PF_TWO_PER_CU : PF_ONE_PER_CU) ? 3 : 1;
-  if (n_work <= PF_ONE_PER_CU) return keys >= PF_LONG ? 4 : keys >= PF_SHARE_64 ? 2 : 1;
-  return keys >= PF_SHARE_64_TWO && n_work <= (few ? PF_THREE_PER_CU : PF_TWO_PER_CU) ? 2 : 1;
+    return keys >= (cached ? PF_CACHED_80 : PF_SHARE_80) &&
+                   n_work <= (few ? PF_TWO_PER_CU : PF_ONE_PER_CU) ? 3 : 1;
+  if (n_work <= PF_ONE_PER_CU)
+    return keys >= PF_LONG ? 4 : keys >= (cached ? PF_CACHED_64 : PF_SHARE_64) ? 2 : 1;
+  if (cached && n_work == slices) return 1;
+  return keys >= (cached ? PF_CACHED_64_TWO : PF_SHARE_64_TWO) &&
+                 n_work <= (few ? PF_THREE_PER_CU : PF_TWO_PER_CU) ? 2 : 1;
 }
 constexpr uint32_t PF_NONE = 0x00ffffffu;  // list entry of a padding column
 constexpr float PF_LOG2E = 1.4426950408889634f;

@@ -243,13 +243,14 @@ def test_prefill_f32_launches(d, H, L):
     assert np.abs(Og - ref).max() <= 1e-5, np.abs(Og - ref).max()
 
 
-# over a cache: one group of waves (many workgroups), two (d = 64, up to 512 where
-# the cache is long) and four (d = 64, few over 1536 rows and more), three (d = 80,
-# few); fp32 with the keys split and with 128 rows a workgroup
+# over a cache: one group of waves (many workgroups, short caches), two (d = 64, up
+# to 512 where the cache is long) and four (d = 64, few over 1409 rows and more),
+# three (d = 80, few); fp32 with the keys split and with 128 rows a workgroup
 @pytest.mark.parametrize("dtype,d,H,L,block", [
     ("bf16", 80, 130, 630, 200), ("bf16", 80, 2, 630, 200), ("bf16", 64, 260, 450, 200),
     ("bf16", 64, 130, 450, 200), ("bf16", 64, 2, 450, 200), ("bf16", 64, 2, 1900, 300),
-    ("bf16", 64, 130, 630, 200), ("f32", 64, 130, 300, 130), ("f32", 64, 5, 300, 130),
+    ("bf16", 64, 130, 630, 200), ("bf16", 64, 130, 895, 200), ("bf16", 64, 130, 896, 200),
+    ("bf16", 80, 2, 640, 200), ("bf16", 64, 2, 383, 200), ("f32", 64, 130, 300, 130), ("f32", 64, 5, 300, 130),
     ("f32", 80, 130, 300, 130), ("f32", 80, 5, 300, 130)])
 def test_prefill_block_launches(dtype, d, H, L, block):
     """Blocks with a ragged last one, spans freed between them and one that
