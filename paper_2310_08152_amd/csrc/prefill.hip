@@ -470,12 +470,16 @@ __device__ __forceinline__ void prefill_attn_body(
   // A <CL> row's output is its own value row, copied before the first tile's
   // rows are: behind those copies its two dependent loads wait for all of them
   // (2048 heads of 128 tokens, 60% freed: 40.1 -> 36.0 us at d = 80, 32.8 -> 31.7
-  // at d = 64; 96 of 300, d = 64, 11.0 -> 10.2), after the loop nothing hides them.
+  // at d = 64; of 64 tokens 24.4 -> 23.2, 19.8 -> 18.6), after the loop nothing
+  // hides them.
   // The row's token is looked up here and the row copied at once where the
   // registers allow it, else while the first entries are on their way (at
-  // d = 64 copied here: 256 heads of 777 tokens 34.2 -> 34.9).
+  // d = 64 copied here: 256 heads of 777 tokens 34.2 -> 34.9).  Groups of waves
+  // have the registers for neither (over a cache at d = 64 four would spill):
+  // they copy it behind the first tile's copies.
   constexpr bool CL_AT_ONCE = NS == 1 && (D == 80 || !BF);
-  const bool is_cl = qrow < L && vu[(int64_t)s * L_meta + qtok] == qtok;
+  bool is_cl = false;
+  auto mark_cl = [&]() { is_cl = qrow < L && vu[(int64_t)s * L_meta + qtok] == qtok; };
   auto copy_cl = [&]() {
     if (!is_cl || grp > 0) return;
     T* const orow = o + (int64_t)bh * os + (int64_t)qrow * D;
@@ -490,6 +494,7 @@ __device__ __forceinline__ void prefill_attn_body(
         else st16(orow + d0, ld16(vrow + d0));
       }
   };
+  if constexpr (NS == 1) mark_cl();
   if constexpr (CL_AT_ONCE) copy_cl();
 
   f32x16 oacc[NDB];
@@ -884,9 +889,13 @@ __device__ __forceinline__ void prefill_attn_body(
     if (NS == 1 || nt > 0) store_entries(0, stg);
     if (nt > 1) store_entries(1, st1);
   }
-  if constexpr (!CL_AT_ONCE) copy_cl();
+  if constexpr (NS == 1 && !CL_AT_ONCE) copy_cl();
   __syncthreads();
   if (NS == 1 || nt > 0) dma_rows(0, kbuf0, vbuf0);
+  if constexpr (NS > 1) {
+    mark_cl();
+    copy_cl();
+  }
 
   wait_vmem();
   __syncthreads();
