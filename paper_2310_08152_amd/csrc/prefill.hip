@@ -476,8 +476,10 @@ __device__ __forceinline__ void prefill_attn_body(
   // registers allow it, else while the first entries are on their way (at
   // d = 64 copied here: 256 heads of 777 tokens 34.2 -> 34.9).  Groups of waves
   // have the registers for neither (over a cache at d = 64 four would spill):
-  // they copy it behind the first tile's copies.
-  constexpr bool CL_AT_ONCE = NS == 1 && (D == 80 || !BF);
+  // they copy it behind the first tile's copies, as fp32 does, whose one buffer
+  // has the wave wait for them next anyway (256 heads of 512 tokens, 40% freed,
+  // d = 64: 109.9 copied here, 104.0 so).
+  constexpr bool CL_LATE = NS > 1 || !BF, CL_AT_ONCE = !CL_LATE && D == 80;
   bool is_cl = false;
   auto mark_cl = [&]() { is_cl = qrow < L && vu[(int64_t)s * L_meta + qtok] == qtok; };
   auto copy_cl = [&]() {
@@ -494,7 +496,7 @@ __device__ __forceinline__ void prefill_attn_body(
         else st16(orow + d0, ld16(vrow + d0));
       }
   };
-  if constexpr (NS == 1) mark_cl();
+  if constexpr (!CL_LATE) mark_cl();
   if constexpr (CL_AT_ONCE) copy_cl();
 
   f32x16 oacc[NDB];
@@ -889,10 +891,10 @@ __device__ __forceinline__ void prefill_attn_body(
     if (NS == 1 || nt > 0) store_entries(0, stg);
     if (nt > 1) store_entries(1, st1);
   }
-  if constexpr (NS == 1 && !CL_AT_ONCE) copy_cl();
+  if constexpr (!CL_LATE && !CL_AT_ONCE) copy_cl();
   __syncthreads();
   if (NS == 1 || nt > 0) dma_rows(0, kbuf0, vbuf0);
-  if constexpr (NS > 1) {
+  if constexpr (CL_LATE) {
     mark_cl();
     copy_cl();
   }
