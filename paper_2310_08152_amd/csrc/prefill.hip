@@ -467,19 +467,18 @@ __device__ __forceinline__ void prefill_attn_body(
     }
   }
 
-  // A <CL> row's output is its own value row, copied before the first tile's
-  // rows are: behind those copies its two dependent loads wait for all of them
-  // (2048 heads of 128 tokens, 60% freed: 40.1 -> 36.0 us at d = 80, 32.8 -> 31.7
-  // at d = 64; of 64 tokens 24.4 -> 23.2, 19.8 -> 18.6), after the loop nothing
-  // hides them.
-  // The row's token is looked up here and the row copied at once where the
-  // registers allow it, else while the first entries are on their way (at
-  // d = 64 copied here: 256 heads of 777 tokens 34.2 -> 34.9).  Groups of waves
-  // have the registers for neither (over a cache at d = 64 four would spill):
-  // they copy it behind the first tile's copies, as fp32 does, whose one buffer
-  // has the wave wait for them next anyway (256 heads of 512 tokens, 40% freed,
-  // d = 64: 109.9 copied here, 104.0 so).
-  constexpr bool CL_LATE = NS > 1 || !BF, CL_AT_ONCE = !CL_LATE && D == 80;
+  // A <CL> row's output is its own value row, copied before the loop: after it
+  // nothing hides the two dependent loads.  Behind the first tile's copies they
+  // wait for all of them, which short lists show (2048 heads of 128 tokens, 60%
+  // freed: 40.1 us so and 36.0 ahead of them at d = 80, 33.9 and 31.4 at d = 64).
+  //   d = 80: here.
+  //   d = 64, short of registers: a slice's only block while its first entries
+  //     are on their way, others behind the copies (256 heads of 777 tokens 33.8
+  //     so, 34.5 ahead of them; 8 x 32 of 1024 46.5 and 48.1).
+  //   groups of waves (over a cache at d = 64 they would spill) and fp32 (256 heads
+  //     of 512 tokens, 40% freed, d = 64: 104.0, and 109.9 here): behind the copies.
+  constexpr bool CL_HERE = NS == 1 && BF && D == 80;
+  const bool cl_late = NS > 1 || !BF || (D == 64 && n_qt > 1);
   bool is_cl = false;
   auto mark_cl = [&]() { is_cl = qrow < L && vu[(int64_t)s * L_meta + qtok] == qtok; };
   auto copy_cl = [&]() {
@@ -496,8 +495,8 @@ __device__ __forceinline__ void prefill_attn_body(
         else st16(orow + d0, ld16(vrow + d0));
       }
   };
-  if constexpr (!CL_LATE) mark_cl();
-  if constexpr (CL_AT_ONCE) copy_cl();
+  if (!cl_late) mark_cl();
+  if constexpr (CL_HERE) copy_cl();
 
   f32x16 oacc[NDB];
 #pragma unroll
@@ -891,10 +890,10 @@ __device__ __forceinline__ void prefill_attn_body(
     if (NS == 1 || nt > 0) store_entries(0, stg);
     if (nt > 1) store_entries(1, st1);
   }
-  if constexpr (!CL_LATE && !CL_AT_ONCE) copy_cl();
+  if (!CL_HERE && !cl_late) copy_cl();
   __syncthreads();
   if (NS == 1 || nt > 0) dma_rows(0, kbuf0, vbuf0);
-  if constexpr (CL_LATE) {
+  if (cl_late) {
     mark_cl();
     copy_cl();
   }
